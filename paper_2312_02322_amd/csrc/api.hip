@@ -2180,10 +2180,19 @@ mqct_status mqct_cross_sections(mqct_context* c, int32_t mem, int64_t B, int32_t
   HIP_TRY(c, hipSetDevice(c->device), "cross_sections");
   mqct_status st;
   const size_t lsz = (size_t)B * n_levels * 8, ssz = (size_t)n_levels * n_levels * 8;
-  if ((st = ensure(c, c->xs[0], lsz + N * 4, "cross_sections")) != MQCT_OK) return st;
+  // the channels of every level, ascending: offsets, then the channels
+  std::vector<int32_t> lists((size_t)n_levels + 1 + N, 0);
+  int32_t* chan = lists.data() + n_levels + 1;
+  for (int n = 0; n < N; ++n) ++lists[level_of_channel[n] + 1];
+  for (int l = 0; l < n_levels; ++l) lists[l + 1] += lists[l];
+  {
+    std::vector<int32_t> at(lists.begin(), lists.begin() + n_levels);
+    for (int n = 0; n < N; ++n) chan[at[level_of_channel[n]]++] = n;
+  }
+  if ((st = ensure(c, c->xs[0], lsz + lists.size() * 4, "cross_sections")) != MQCT_OK) return st;
   double* lsum = (double*)c->xs[0].p;
   int32_t* dlev = (int32_t*)((char*)c->xs[0].p + lsz);
-  HIP_TRY(c, hipMemcpyAsync(dlev, level_of_channel, N * 4, hipMemcpyHostToDevice, c->stream),
+  HIP_TRY(c, hipMemcpyAsync(dlev, lists.data(), lists.size() * 4, hipMemcpyHostToDevice, c->stream),
           "cross_sections");
   const double *dP = P, *db = b;
   const int32_t* dil = init_level;
@@ -2202,7 +2211,8 @@ mqct_status mqct_cross_sections(mqct_context* c, int32_t mem, int64_t B, int32_t
     dil = (const int32_t*)(base + (size_t)B * N * 8 + B * 8);
     dsig = (double*)c->xs[2].p;
   }
-  HIP_TRY(c, launch_xsec(B, N, dP, db, dil, dlev, n_levels, b_max, lsum, dsig, c->stream),
+  HIP_TRY(c, launch_xsec(B, N, dP, db, dil, dlev, dlev + n_levels + 1, n_levels, b_max, lsum, dsig,
+                         c->stream),
           "cross_sections");
   if (mem == MQCT_MEM_HOST) {
     HIP_TRY(c, hipMemcpyAsync(sigma, dsig, ssz, hipMemcpyDeviceToHost, c->stream), "cross_sections");

@@ -358,10 +358,12 @@ hipError_t run_columns(const DevSystem* d_systems, const DevSystem& hs, const Tr
 // Streaming read of `bytes` (a multiple of 16) at buf (measure.hip).
 hipError_t launch_read_probe(const void* buf, int64_t bytes, int n_cu, hipStream_t s);
 
-// Cross sections on the device.
-hipError_t launch_xsec(int64_t B, int N, const double* P, const double* b, const int32_t* init_level,
-                       const int32_t* level_of_channel, int n_levels, double b_max,
-                       double* level_sums /*[B][n_levels]*/, double* sigma, hipStream_t s);
+// Cross sections on the device: chan[off[L] .. off[L+1]-1] are the channels of
+// level L, ascending.
+hipError_t launch_xsec(int64_t B, int N, const double* P, const double* b,
+                       const int32_t* init_level, const int32_t* off, const int32_t* chan,
+                       int n_levels, double b_max, double* level_sums /*[B][n_levels]*/,
+                       double* sigma, hipStream_t s);
 
 // cross-section post-processing (postproc.hip), device pointers
 hipError_t launch_xs_symmetrize(int nE, int L, const double* g, const double* sigma, double* sym,
