@@ -7,18 +7,19 @@
 // Tables: the stored elements in row order (CSR, each row's columns ascending),
 // their values and natural-spline second derivatives per knot, [K][nnz]
 // (complex interleaved).  A group of columns that shares a path (at most
-// COL_MAX) keeps its amplitudes as rows of CT complex FP64 values, [N][CT]
-// (CT: the columns padded to even), so the product's gather of a coupled row m
-// reads CT contiguous values.
+// COL_MAX) keeps its amplitudes in column tiles: tile k holds columns k TW ..
+// k TW + tw - 1 of every row, [N][tw] complex, so the product's gather of a
+// coupled row m reads tw contiguous values.
 //
-// One launch per RK4 stage: a wave takes one row of one group, two columns per
-// lane.  A row's elements are read 64 at a time, one per lane, and turned into
-// the spline value at the stage's R in FP64; then they are broadcast one by one
-// while every lane gathers its columns of the coupled row's phased amplitudes
-// c_m = e^{-iE_m t} a_m.  The J_x term, the row's phase, the RK4 update and the
-// phased amplitudes of the next stage follow in the same kernel (Eq. 5).  The
-// classical path is driven by U(R) alone (AT), so it is integrated once per
-// group beforehand (Eqs. 7-9 with the driver's force), one thread per group.
+// One launch per RK4 stage: a wave takes one row of one tile.  A row's elements
+// are read 64 at a time, one per lane, turned into the spline value at the stage's
+// R in FP64 and left in LDS; then LPT lanes (two columns each) per element gather
+// the coupled row's phased amplitudes c_m = e^{-iE_m t} a_m, 64 / LPT elements
+// side by side, whose sums meet at the end of the row.  The J_x term, the row's
+// phase, the RK4 update and the phased amplitudes of the next stage follow in the
+// same kernel (Eq. 5).  The classical path is driven by U(R) alone (AT), so it is
+// integrated once per group beforehand (Eqs. 7-9 with the driver's force), one
+// thread per group.
 #include "device.h"
 
 #include <math.h>
@@ -31,10 +32,12 @@ namespace {
 
 constexpr int CB = 512;         // threads of the row kernels
 constexpr int CW = CB / 64;
-constexpr int ROWS_PER_WAVE = 1;
-constexpr int ROWS_PER_WG = CW * ROWS_PER_WAVE;
+constexpr int ROWS_PER_WG = CW; // one row per wave
+constexpr int OUT_ROWS = 64;    // rows per workgroup of col_out
 constexpr int NXCD = 8;         // dies of the device; workgroups are dealt to them round-robin
-constexpr int GATHER_UNROLL = 8;
+constexpr int COL_JX = 2;        // entries of a J_x row requested ahead of the product
+constexpr int COL_TILE = 64;     // most columns of a tile (two per lane, 32 lanes)
+constexpr int COL_GU32 = 8, COL_GU64 = 4;   // gathers in flight per lane, FP32 / FP64
 
 inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -151,19 +154,25 @@ struct ColArgs {
   const TrajIn* traj;       // records in group order
   const ColGroup* groups;   // [G]
   int G, N, CT;
-  int64_t nchunk;           // row chunks of one group
+  int TW;                   // columns per tile (even); the last tile holds the rest
+  int nt;                   // tiles of a group
+  int64_t nchunk;           // row chunks of one tile in the stage kernel
+  int64_t nout;             // row chunks of one group in col_out
   ColStage* st;             // stage records, group g from groups[g].stage_off
   double* fin;              // [G][8]: R, Phi, P_R, P_Phi, theta, P_theta, E0, E1
   int* gstatus;             // [G]
-  double2* A0;              // [G][N][CT] amplitudes at the start of the step
-  double2* ACC;             // [G][N][CT] RK4 accumulator
-  double2* CUR[2];          // [G][N][CT] stage amplitudes (input, next)
-  void* C[2];               // [G][N][CT] phased stage amplitudes in the table precision
-  double* part;             // [G][nchunk][CT] partial norms
+  // [G][tiles][N][tw]:
+  double2* A0;              // amplitudes at the start of the step (the input of stage 0)
+  double2* ACC;             // RK4 accumulator
+  double2* CUR[2];          // amplitudes of stages 2 (buffer 0) and 1, 3 (buffer 1)
+  void* C[2];               // phased stage amplitudes in the table precision
+  double* part;             // [G][nout][CT] partial norms
 };
 
-__device__ __forceinline__ int64_t cidx(const ColArgs& a, int g, int n, int col) {
-  return ((int64_t)g * a.N + n) * a.CT + col;
+// Columns of tile k, and where its rows start.
+__device__ __forceinline__ int tile_w(const ColArgs& a, int k) { return min(a.TW, a.CT - k * a.TW); }
+__device__ __forceinline__ int64_t tile_at(const ColArgs& a, int g, int k) {
+  return (int64_t)a.N * ((int64_t)g * a.CT + (int64_t)k * a.TW);
 }
 
 // Stage times of step j: t_j + cf_s h with t_j = t0 + j h (Eq. 4's time, RK4 stages).
@@ -271,10 +280,9 @@ __global__ void __launch_bounds__(CB) col_init(ColArgs a, const double* __restri
       if (tj.flags & TRAJ_HAS_A0) v = ((const double2*)a0_all)[tj.amp_off + n];
       else if (n == tj.init_channel) v = make_double2(1.0, 0.0);
     }
-    const int64_t o = cidx(a, g, n, col);
+    const int k = col / a.TW;
+    const int64_t o = tile_at(a, g, k) + (int64_t)n * tile_w(a, k) + (col - k * a.TW);
     a.A0[o] = v;
-    a.CUR[0][o] = v;
-    a.ACC[o] = make_double2(0.0, 0.0);
     c[o] = CV<CS>::make(cs * v.x + sn * v.y, cs * v.y - sn * v.x);
   }
 }
@@ -285,18 +293,55 @@ __device__ __forceinline__ double rl(double v, int l) {
   return __hiloint2double(hi, lo);
 }
 
+// Loads and stores of data that is used once per stage.
+typedef double dnt2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double2 load_once(const double2* p) {
+  const dnt2 v = __builtin_nontemporal_load((const dnt2*)p);
+  return make_double2(v.x, v.y);
+}
+__device__ __forceinline__ void store_once(double2* p, double2 v) {
+  __builtin_nontemporal_store(dnt2{v.x, v.y}, (dnt2*)p);
+}
+
+// One element of a row in LDS: its column and its spline value in the precision of
+// the products.
+template <typename CS, bool CPLX> struct ColEnt;
+template <> struct alignas(8) ColEnt<float, false> { int m; float v; };
+template <> struct alignas(16) ColEnt<float, true> { int m; float v, w; int pad; };
+template <> struct alignas(16) ColEnt<double, false> { double v; int m; int pad; };
+template <> struct alignas(16) ColEnt<double, true> { double v, w; int m; int pad[3]; };
+
 // One RK4 stage s of step j for every group still running (see the top of the
 // file).  S: table precision; CPLX: complex tables; CS: precision of the phased
 // amplitudes (and of the products: FP32 products over one 64-element chunk,
-// then FP64 sums).  in = stage parity.
-template <typename S, bool CPLX, typename CS>
+// then FP64 sums).
+//
+// Bound by the L2's line rate and latency: the gathers read a kept element's
+// coupled row, 8 or 16 B x columns, which stays in a die's 4 MB L2 only if the rows
+// of one m-block do.  With all 100 columns side by side the largest blocks (5,300
+// rows x 800 B) did not, and the misses bound the kernel; a tile's do (19 M misses
+// of 129 M requests instead of 38 M), for the price of reading the tables once per
+// tile.  Rows are dealt to the dies in contiguous ranges of one tile.  Lanes beyond
+// a tile's columns would idle, so 64 / LPT elements run side by side.  What the
+// row's update reads, and the next chunk's elements, are requested before the
+// products (a wave's life is a chain of such round trips); the step's start and
+// the accumulator, read once, stay out of the caches.  206,700 states, 13.1 M
+// elements, 100 columns: FP32 1.38 ms a stage before, 1.10 now, FP64 2.35 and 1.80;
+// N = 30,000, 2 x 37 columns, FP64: 0.288 and 0.158.
+template <typename S, bool CPLX, typename CS, int LPT>
 __global__ void __launch_bounds__(CB)
 col_stage(ColArgs a, int64_t j, int s) {
-  const int64_t per = (a.G * a.nchunk + NXCD - 1) / NXCD;
+  constexpr int EP = 64 / LPT;      // elements side by side
+  constexpr int GU = sizeof(CS) == 4 ? COL_GU32 : COL_GU64;   // gathers in flight per lane
+  using Ent = ColEnt<CS, CPLX>;
+  __shared__ Ent ents[CW][64];
+  const int64_t items = (int64_t)a.G * a.nt * a.nchunk;
+  const int64_t per = (items + NXCD - 1) / NXCD;
   const int64_t pos = (int64_t)(blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
-  if (blockIdx.x / NXCD >= per || pos >= (int64_t)a.G * a.nchunk) return;
-  const int g = (int)(pos / a.nchunk);
-  const int64_t chunk = pos % a.nchunk;
+  if (blockIdx.x / NXCD >= per || pos >= items) return;
+  const int gt = (int)(pos / a.nchunk);
+  const int64_t chunk = pos - (int64_t)gt * a.nchunk;
+  const int g = gt / a.nt, k = gt - g * a.nt;
   const ColGroup gr = a.groups[g];
   if (j >= gr.n_steps) return;
   const TrajIn t0r = a.traj[gr.first];
@@ -306,16 +351,20 @@ col_stage(ColArgs a, int64_t j, int s) {
   const double tj = t0r.t0 + (double)j * h;
   const double t = tj + col_cf(s) * h;
   const double tn = s < 3 ? tj + col_cf(s + 1) * h : t0r.t0 + (double)(j + 1) * h;
-  const int in = s & 1, outb = in ^ 1;
   using C2 = typename CV<CS>::T;
-  const C2* __restrict__ cin = (const C2*)a.C[in];
-  C2* __restrict__ cout = (C2*)a.C[outb];
-  const double2* __restrict__ curin = a.CUR[in];
-  double2* __restrict__ curout = a.CUR[outb];
+  const int64_t base = tile_at(a, g, k);
+  const int tw = tile_w(a, k);
+  const C2* __restrict__ cin = (const C2*)a.C[s & 1] + base;
+  C2* __restrict__ cout = (C2*)a.C[(s & 1) ^ 1] + base;
+  const double2* __restrict__ curin = (s == 0 ? a.A0 : a.CUR[s & 1]) + base;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c0 = 2 * lane;
-  const bool act = c0 < a.CT;
+  const int64_t nl = chunk * ROWS_PER_WG + wave;
+  if (nl >= a.N) return;
+  const int n = (int)nl;
+  const int grp = lane / LPT;
+  const int c0 = 2 * (lane % LPT);
+  const bool act = c0 < tw;
   const int64_t nnz = sy.knot_stride;
   constexpr int NC = CPLX ? 2 : 1;
   const S* __restrict__ V0 = (const S*)sy.M + (int64_t)rec.k * nnz * NC;
@@ -323,143 +372,208 @@ col_stage(ColArgs a, int64_t j, int s) {
   const S* __restrict__ D0 = (const S*)sy.M2 + (int64_t)rec.k * nnz * NC;
   const S* __restrict__ D1 = D0 + nnz * NC;
   const double w0 = rec.w[0], w1 = rec.w[1], w2 = rec.w[2], w3 = rec.w[3];
-  const C2* cg = cin + (int64_t)g * a.N * a.CT + (act ? c0 : 0);
-  for (int r = 0; r < ROWS_PER_WAVE; ++r) {
-    const int64_t nl = chunk * ROWS_PER_WG + (int64_t)wave * ROWS_PER_WAVE + r;
-    if (nl >= a.N) break;
-    const int n = (int)nl;
-    const int rs = sy.csr_row[n], re = sy.csr_row[n + 1];
-    double y0x = 0.0, y0y = 0.0, y1x = 0.0, y1y = 0.0;
-    for (int e0 = rs; e0 < re; e0 += 64) {
-      const int e = e0 + lane;
-      int m = n;
-      double mr = 0.0, mi = 0.0;
-      if (e < re) {
-        m = sy.csr_col[e];
-        mr = w0 * (double)V0[(int64_t)e * NC] + w1 * (double)V1[(int64_t)e * NC] +
-             w2 * (double)D0[(int64_t)e * NC] + w3 * (double)D1[(int64_t)e * NC];
-        if constexpr (CPLX)
-          mi = w0 * (double)V0[(int64_t)e * NC + 1] + w1 * (double)V1[(int64_t)e * NC + 1] +
-               w2 * (double)D0[(int64_t)e * NC + 1] + w3 * (double)D1[(int64_t)e * NC + 1];
-      }
-      const int cnt = min(64, re - e0);
-      CS p0x = 0, p0y = 0, p1x = 0, p1y = 0;
-      for (int i = 0; i < cnt; i += GATHER_UNROLL) {
-        C2 g0[GATHER_UNROLL], g1[GATHER_UNROLL];
-        CS br[GATHER_UNROLL], bi[GATHER_UNROLL];
+  const C2* cg = cin + (act ? c0 : 0);
+  Ent* ent = ents[wave];
+  const int rs = sy.csr_row[n], re = sy.csr_row[n + 1];
+  // what the row's update reads -- this lane's column of the step's start, of the
+  // accumulator and of the rows coupled by J_x -- is requested before the product
+  const bool upd = act && grp < 2;      // lane group 0 updates a pair's first column, 1 its second
+  const int col = c0 + (grp & 1);
+  const int64_t o = (int64_t)n * tw + col, ob = base + o;
+  const int jw = sy.jx_w;
+  double2 av0 = make_double2(0.0, 0.0), ac = av0, jav[COL_JX];
+  double jv[COL_JX];
 #pragma unroll
-        for (int u = 0; u < GATHER_UNROLL; ++u) {
-          // entries past the chunk's count read the row's own amplitudes and add zero
-          const int l = min(i + u, cnt - 1);
-          const int mu = __builtin_amdgcn_readlane(m, l);
-          const double vr = i + u < cnt ? rl(mr, l) : 0.0;
-          br[u] = (CS)vr;
-          if constexpr (CPLX) bi[u] = (CS)(i + u < cnt ? rl(mi, l) : 0.0);
-          const C2* src = cg + (int64_t)mu * a.CT;
-          if (act) {
-            g0[u] = src[0];
-            g1[u] = src[1];
-          } else {
-            g0[u] = CV<CS>::make(0.0, 0.0);
-            g1[u] = CV<CS>::make(0.0, 0.0);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < GATHER_UNROLL; ++u) {
-          p0x += br[u] * g0[u].x; p0y += br[u] * g0[u].y;
-          p1x += br[u] * g1[u].x; p1y += br[u] * g1[u].y;
-          if constexpr (CPLX) {
-            p0x -= bi[u] * g0[u].y; p0y += bi[u] * g0[u].x;
-            p1x -= bi[u] * g1[u].y; p1y += bi[u] * g1[u].x;
-          }
-        }
-      }
-      y0x += (double)p0x; y0y += (double)p0y; y1x += (double)p1x; y1y += (double)p1y;
-    }
-    if (!act) continue;
-    double sn, cs;
-    sincos(sy.E[n] * t, &sn, &cs);
-    double sn2, cs2;
-    sincos(sy.E[n] * tn, &sn2, &cs2);
-    const double yv[2][2] = {{y0x, y0y}, {y1x, y1y}};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int col = c0 + q;
-      if (col >= a.CT) break;
-      // J_x a of this row (couples states of equal energy, Eq. 5)
-      double xx = 0.0, xy = 0.0;
-      for (int w = 0; w < sy.jx_w; ++w) {
-        const int jc = sy.jx_col[(int64_t)n * sy.jx_w + w];
-        const double jv = sy.jx_val[(int64_t)n * sy.jx_w + w];
-        const double2 av = curin[cidx(a, g, jc, col)];
-        xx = fma(jv, av.x, xx);
-        xy = fma(jv, av.y, xy);
-      }
-      // da/dt = -i (e^{iE_n t} (M c)_n + Phidot (J_x a)_n)
-      const double Gx = cs * yv[q][0] - sn * yv[q][1] + rec.om * xx;
-      const double Gy = cs * yv[q][1] + sn * yv[q][0] + rec.om * xy;
-      const double fx = Gy, fy = -Gx;
-      const int64_t o = cidx(a, g, n, col);
-      const double2 av0 = a.A0[o];
-      double2 nx;
-      if (s == 0) {
-        a.ACC[o] = make_double2(fx, fy);
-        nx = make_double2(fma(0.5 * h, fx, av0.x), fma(0.5 * h, fy, av0.y));
-      } else if (s < 3) {
-        const double2 ac = a.ACC[o];
-        a.ACC[o] = make_double2(fma(2.0, fx, ac.x), fma(2.0, fy, ac.y));
-        const double cfn = s == 1 ? 0.5 * h : h;
-        nx = make_double2(fma(cfn, fx, av0.x), fma(cfn, fy, av0.y));
-      } else {
-        const double2 ac = a.ACC[o];
-        nx = make_double2(fma(h / 6.0, ac.x + fx, av0.x), fma(h / 6.0, ac.y + fy, av0.y));
-        a.A0[o] = nx;
-      }
-      curout[o] = nx;
-      cout[o] = CV<CS>::make(cs2 * nx.x + sn2 * nx.y, cs2 * nx.y - sn2 * nx.x);
+  for (int w = 0; w < COL_JX; ++w) {
+    jav[w] = av0;
+    jv[w] = 0.0;
+    if (upd && w < jw) {
+      jv[w] = sy.jx_val[(int64_t)n * jw + w];
+      jav[w] = curin[(int64_t)sy.jx_col[(int64_t)n * jw + w] * tw + col];
     }
   }
+  if (upd) {
+    av0 = load_once(a.A0 + ob);
+    if (s > 0) ac = load_once(a.ACC + ob);
+  }
+  // the row's phases at t (even lanes) and tn (odd lanes)
+  double sns, css;
+  sincos(sy.E[n] * ((lane & 1) ? tn : t), &sns, &css);
+  // a chunk's elements, one per lane; the next chunk's are requested before the
+  // current one's products
+  auto fetch = [&](int e, int& m, S (&x)[4], S (&xi)[4]) {
+    m = n;         // entries past the row's end read the row's own amplitudes and add zero
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = xi[q] = 0;
+    if (e < re) {
+      m = sy.csr_col[e];
+      const S* const T[4] = {V0, V1, D0, D1};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        x[q] = T[q][(int64_t)e * NC];
+        if constexpr (CPLX) xi[q] = T[q][(int64_t)e * NC + 1];
+      }
+    }
+  };
+  int mq;
+  S xq[4], xiq[4];
+  fetch(rs + lane, mq, xq, xiq);
+  double y0x = 0.0, y0y = 0.0, y1x = 0.0, y1y = 0.0;
+  for (int e0 = rs; e0 < re; e0 += 64) {
+    Ent en{};
+    en.m = mq;
+    en.v = (CS)(w0 * (double)xq[0] + w1 * (double)xq[1] + w2 * (double)xq[2] + w3 * (double)xq[3]);
+    if constexpr (CPLX)
+      en.w = (CS)(w0 * (double)xiq[0] + w1 * (double)xiq[1] + w2 * (double)xiq[2] +
+                  w3 * (double)xiq[3]);
+    __builtin_amdgcn_wave_barrier();   // the previous chunk's entries are consumed (in order)
+    ent[lane] = en;
+    __builtin_amdgcn_wave_barrier();
+    if (e0 + 64 < re) fetch(e0 + 64 + lane, mq, xq, xiq);
+    const int steps = (min(64, re - e0) + EP - 1) / EP;
+    CS p0x = 0, p0y = 0, p1x = 0, p1y = 0;
+    for (int i = 0; i < steps; i += GU) {
+      // i + u < LPT (a multiple of GU), so the entries stay within the 64
+      C2 g0[GU], g1[GU];
+      CS br[GU], bi[GU];
+#pragma unroll
+      for (int u = 0; u < GU; ++u) {
+        const Ent x = ent[(i + u) * EP + grp];
+        br[u] = x.v;
+        if constexpr (CPLX) bi[u] = x.w;
+        const C2* src = cg + (int64_t)x.m * tw;
+        if constexpr (sizeof(CS) == 4) {
+          // the pair's 16 bytes at once (tw and c0 are even, the arrays 256-byte aligned)
+          const float4 v = *(const float4*)src;
+          g0[u] = C2{v.x, v.y};
+          g1[u] = C2{v.z, v.w};
+        } else {
+          g0[u] = src[0];
+          g1[u] = src[1];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < GU; ++u) {
+        p0x += br[u] * g0[u].x; p0y += br[u] * g0[u].y;
+        p1x += br[u] * g1[u].x; p1y += br[u] * g1[u].y;
+        if constexpr (CPLX) {
+          p0x -= bi[u] * g0[u].y; p0y += bi[u] * g0[u].x;
+          p1x -= bi[u] * g1[u].y; p1y += bi[u] * g1[u].x;
+        }
+      }
+    }
+    y0x += (double)p0x; y0y += (double)p0y; y1x += (double)p1x; y1y += (double)p1y;
+  }
+  // the side-by-side sums of each column pair, then one column per lane
+#pragma unroll
+  for (int x = LPT; x < 64; x <<= 1) {
+    y0x += __shfl_xor(y0x, x, 64); y0y += __shfl_xor(y0y, x, 64);
+    y1x += __shfl_xor(y1x, x, 64); y1y += __shfl_xor(y1y, x, 64);
+  }
+  const double sn = rl(sns, 0), cs = rl(css, 0), sn2 = rl(sns, 1), cs2 = rl(css, 1);
+  if (!upd) return;
+  const double yx = grp ? y1x : y0x, yy = grp ? y1y : y0y;
+  // J_x a of this row (couples states of equal energy, Eq. 5)
+  double xx = 0.0, xy = 0.0;
+#pragma unroll
+  for (int w = 0; w < COL_JX; ++w) {
+    xx = fma(jv[w], jav[w].x, xx);
+    xy = fma(jv[w], jav[w].y, xy);
+  }
+  for (int w = COL_JX; w < jw; ++w) {
+    const double2 av = curin[(int64_t)sy.jx_col[(int64_t)n * jw + w] * tw + col];
+    const double jvw = sy.jx_val[(int64_t)n * jw + w];
+    xx = fma(jvw, av.x, xx);
+    xy = fma(jvw, av.y, xy);
+  }
+  // da/dt = -i (e^{iE_n t} (M c)_n + Phidot (J_x a)_n)
+  const double Gx = cs * yx - sn * yy + rec.om * xx;
+  const double Gy = cs * yy + sn * yx + rec.om * xy;
+  const double fx = Gy, fy = -Gx;
+  double2 nx;
+  if (s == 0) {
+    store_once(a.ACC + ob, make_double2(fx, fy));
+    nx = make_double2(fma(0.5 * h, fx, av0.x), fma(0.5 * h, fy, av0.y));
+    a.CUR[1][ob] = nx;
+  } else if (s < 3) {
+    store_once(a.ACC + ob, make_double2(fma(2.0, fx, ac.x), fma(2.0, fy, ac.y)));
+    const double cfn = s == 1 ? 0.5 * h : h;
+    nx = make_double2(fma(cfn, fx, av0.x), fma(cfn, fy, av0.y));
+    a.CUR[(s & 1) ^ 1][ob] = nx;
+  } else {
+    // the next step's stage 0 reads its input from A0 (no other row reads A0 here)
+    nx = make_double2(fma(h / 6.0, ac.x + fx, av0.x), fma(h / 6.0, ac.y + fy, av0.y));
+    store_once(a.A0 + ob, nx);
+  }
+  cout[o] = CV<CS>::make(cs2 * nx.x + sn2 * nx.y, cs2 * nx.y - sn2 * nx.x);
 }
 
-// Final probabilities and amplitudes of every column, and partial norms per
-// chunk of rows (summed in order by col_fin).
-__global__ void __launch_bounds__(CB) col_out(ColArgs a, TrajOut out) {
-  const int64_t item = (int64_t)blockIdx.x * CW + (threadIdx.x >> 6);
+// Final probabilities and amplitudes of every column, and its norm over OUT_ROWS
+// rows (summed by col_fin).  The results are stored column after column, the
+// amplitudes row after row: 64 rows x 32 columns turn in LDS, so both sides are
+// read and written in whole lines (0.58 ms for 206,350 x 100 by strided stores).
+constexpr int OUT_COLS = 32;
+__global__ void __launch_bounds__(256) col_out(ColArgs a, TrajOut out) {
+  __shared__ double2 buf[OUT_COLS][OUT_ROWS + 1];
+  const int64_t item = blockIdx.x;
+  const int nsub = (a.CT + OUT_COLS - 1) / OUT_COLS;
+  const int sub = (int)(item % nsub);
+  const int64_t gc = item / nsub;
+  const int g = (int)(gc / a.nout);
+  const int64_t chunk = gc - (int64_t)g * a.nout;
+  const ColGroup gr = a.groups[g];
+  const int64_t n0 = chunk * OUT_ROWS;
+  const int rows = (int)min((int64_t)OUT_ROWS, a.N - n0);
+  const int cl = threadIdx.x % OUT_COLS, col = sub * OUT_COLS + cl;
+  if (col < a.CT) {
+    const int k = col / a.TW, tw = tile_w(a, k);
+    const double2* src = a.A0 + tile_at(a, g, k) + (col - k * a.TW);
+    for (int r = threadIdx.x / OUT_COLS; r < rows; r += 256 / OUT_COLS)
+      buf[cl][r] = src[(n0 + r) * tw];
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63;
-  if (item >= (int64_t)a.G * a.nchunk) return;
-  const int g = (int)(item / a.nchunk);
-  const int64_t chunk = item % a.nchunk;
-  const ColGroup gr = a.groups[g];
-  for (int col = lane; col < a.CT; col += 64) {
-    double nrm = 0.0;
-    const bool real = col < gr.count;
-    const TrajIn tj = a.traj[gr.first + (real ? col : 0)];
-    for (int r = 0; r < ROWS_PER_WG; ++r) {
-      const int64_t n = chunk * ROWS_PER_WG + r;
-      if (n >= a.N) break;
-      const double2 v = a.A0[cidx(a, g, (int)n, col)];
-      const double p = v.x * v.x + v.y * v.y;
-      nrm += p;
-      if (real) {
-        if (out.P) out.P[tj.amp_off + n] = p;
-        if (out.a_final) ((double2*)out.a_final)[tj.amp_off + n] = v;
+  for (int c = threadIdx.x >> 6; c < OUT_COLS; c += 4) {
+    const int cc = sub * OUT_COLS + c;
+    if (cc >= a.CT) break;
+    double p[1] = {0.0};
+    if (lane < rows) {
+      const double2 v = buf[c][lane];
+      p[0] = v.x * v.x + v.y * v.y;
+      if (cc < gr.count) {
+        const int64_t o = a.traj[gr.first + cc].amp_off + n0 + lane;
+        if (out.P) out.P[o] = p[0];
+        if (out.a_final) ((double2*)out.a_final)[o] = v;
       }
     }
-    a.part[((int64_t)g * a.nchunk + chunk) * a.CT + col] = nrm;
+    wave_sum<1>(p);
+    if (lane == 0) a.part[((int64_t)g * a.nout + chunk) * a.CT + cc] = p[0];
   }
 }
 
-// Per column: the norm (partials summed in row order), the path's end state and
-// diagnostics (AT: the driven energy P_R^2/2mu + P_Phi^2/(2 mu R^2) + U(R) and P_Phi).
-__global__ void col_fin(ColArgs a, TrajOut out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int g = (int)(i / COL_MAX), col = (int)(i % COL_MAX);
-  if (g >= a.G) return;
+// Per column: the norm (16 runs of partials, then the runs in order), the path's
+// end state and diagnostics (AT: the driven energy P_R^2/2mu + P_Phi^2/(2 mu R^2) +
+// U(R) and P_Phi).  One workgroup per group and 64 columns.
+constexpr int FIN_SEG = 16;
+__global__ void __launch_bounds__(64 * FIN_SEG) col_fin(ColArgs a, TrajOut out) {
+  __shared__ double seg[FIN_SEG][64];
+  const int g = blockIdx.x, lane = threadIdx.x & 63, sg = threadIdx.x >> 6;
+  const int col = blockIdx.y * 64 + lane;
   const ColGroup gr = a.groups[g];
-  if (col >= gr.count) return;
+  const bool real = col < gr.count;
+  double s = 0.0;
+  if (real) {
+    const int64_t c1 = a.nout * (sg + 1) / FIN_SEG;
+#pragma unroll 8
+    for (int64_t c = a.nout * sg / FIN_SEG; c < c1; ++c)
+      s += a.part[((int64_t)g * a.nout + c) * a.CT + col];
+  }
+  seg[sg][lane] = s;
+  __syncthreads();
+  if (sg > 0 || !real) return;
   const TrajIn tj = a.traj[gr.first + col];
   double nrm = 0.0;
-  for (int64_t c = 0; c < a.nchunk; ++c) nrm += a.part[((int64_t)g * a.nchunk + c) * a.CT + col];
+  for (int q = 0; q < FIN_SEG; ++q) nrm += seg[q][lane];
   const double* f = a.fin + (int64_t)g * 8;
   const int64_t id = tj.id;
   if (out.classical) {
@@ -473,6 +587,23 @@ __global__ void col_fin(ColArgs a, TrajOut out) {
   if (out.norm_err) out.norm_err[id] = nrm - 1.0;
   if (out.energy_err) out.energy_err[id] = (f[7] - f[6]) / fabs(f[6]);
   if (out.angmom_err) out.angmom_err[id] = 0.0;   // no torque: P_Phi is constant
+}
+
+// Columns per tile: tiles of equal width, even (two columns per lane), as few as
+// hold COL_TILE columns each.  Narrower tiles waste lanes and repeat the row's
+// fixed work: 100 columns, 206,700 states, per 32 stages, FP32 35.6 ms as 2 x 50,
+// 43.1 as one, 46.3 as 4 x 25; FP64 58.0 as 2 x 50, 75.6 as 3 x 34; N = 30,000 and
+// 37 columns, FP64, 48 stages: 7.9 ms as one, 10.3 as 2 x 20.
+int col_tile(int CT) {
+  const int nt = (CT + COL_TILE - 1) / COL_TILE;
+  return ((CT + nt - 1) / nt + 1) & ~1;
+}
+
+template <typename S, bool CPLX, typename CS>
+void launch_stage(const ColArgs& a, unsigned grid, int64_t j, int st, hipStream_t s) {
+  if (a.TW <= 16) col_stage<S, CPLX, CS, 8><<<grid, CB, 0, s>>>(a, j, st);
+  else if (a.TW <= 32) col_stage<S, CPLX, CS, 16><<<grid, CB, 0, s>>>(a, j, st);
+  else col_stage<S, CPLX, CS, 32><<<grid, CB, 0, s>>>(a, j, st);
 }
 
 }  // namespace
@@ -508,14 +639,14 @@ hipError_t launch_csr_cast_f32(const double* in, int64_t n, float* out, hipStrea
 
 size_t columns_workspace_bytes(int G, int N, int CT, int64_t stages, bool fp32) {
   const size_t v = (size_t)G * N * CT;
-  const int64_t nchunk = (N + ROWS_PER_WG - 1) / ROWS_PER_WG;
+  const int64_t nout = (N + OUT_ROWS - 1) / OUT_ROWS;
   size_t b = 0;
   b += al((size_t)G * sizeof(ColGroup));
   b += al((size_t)std::max<int64_t>(stages, 1) * sizeof(ColStage));
   b += al((size_t)G * 8 * 8) + al((size_t)G * 4);
   b += 4 * al(v * 16);
   b += 2 * al(v * (fp32 ? 8 : 16));
-  b += al((size_t)G * nchunk * CT * 8);
+  b += al((size_t)G * nout * CT * 8);
   return b;
 }
 
@@ -536,7 +667,10 @@ hipError_t run_columns(const DevSystem* d_systems, const DevSystem& hs, const Tr
   a.G = G;
   a.N = N;
   a.CT = CT;
+  a.TW = col_tile(CT);
+  a.nt = (CT + a.TW - 1) / a.TW;
   a.nchunk = (N + ROWS_PER_WG - 1) / ROWS_PER_WG;
+  a.nout = (N + OUT_ROWS - 1) / OUT_ROWS;
   char* p = (char*)wsp;
   auto take = [&](size_t bytes) { void* q = p; p += al(bytes); return q; };
   ColGroup* dg = (ColGroup*)take((size_t)G * sizeof(ColGroup));
@@ -551,7 +685,7 @@ hipError_t run_columns(const DevSystem* d_systems, const DevSystem& hs, const Tr
   a.CUR[1] = (double2*)take(v * 16);
   a.C[0] = take(v * (fp32 ? 8 : 16));
   a.C[1] = take(v * (fp32 ? 8 : 16));
-  a.part = (double*)take((size_t)G * a.nchunk * CT * 8);
+  a.part = (double*)take((size_t)G * a.nout * CT * 8);
   hipError_t e;
   if ((e = hipMemcpyAsync(dg, groups.data(), (size_t)G * sizeof(ColGroup), hipMemcpyHostToDevice,
                           s)) != hipSuccess)
@@ -561,18 +695,20 @@ hipError_t run_columns(const DevSystem* d_systems, const DevSystem& hs, const Tr
   if (fp32) col_init<float><<<init_grid, CB, 0, s>>>(a, d_a0);
   else col_init<double><<<init_grid, CB, 0, s>>>(a, d_a0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int64_t items = (int64_t)G * a.nchunk;
+  const int64_t items = (int64_t)G * a.nt * a.nchunk;
+  const int64_t outs = (int64_t)G * a.nout * ((CT + OUT_COLS - 1) / OUT_COLS);
+  if (items + NXCD > 0x7fffffffLL || outs > 0x7fffffffLL) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((items + NXCD - 1) / NXCD * NXCD);
   for (int64_t j = 0; j < nmax; ++j)
     for (int st = 0; st < 4; ++st) {
-      if (hs.dtype == R64) col_stage<double, false, double><<<grid, CB, 0, s>>>(a, j, st);
-      else if (hs.dtype == C128) col_stage<double, true, double><<<grid, CB, 0, s>>>(a, j, st);
-      else if (hs.dtype == R32) col_stage<float, false, float><<<grid, CB, 0, s>>>(a, j, st);
-      else col_stage<float, true, float><<<grid, CB, 0, s>>>(a, j, st);
+      if (hs.dtype == R64) launch_stage<double, false, double>(a, grid, j, st, s);
+      else if (hs.dtype == C128) launch_stage<double, true, double>(a, grid, j, st, s);
+      else if (hs.dtype == R32) launch_stage<float, false, float>(a, grid, j, st, s);
+      else launch_stage<float, true, float>(a, grid, j, st, s);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-  col_out<<<(unsigned)((items + CW - 1) / CW), CB, 0, s>>>(a, out);
-  col_fin<<<(unsigned)(((int64_t)G * COL_MAX + 255) / 256), 256, 0, s>>>(a, out);
+  col_out<<<(unsigned)outs, 256, 0, s>>>(a, out);
+  col_fin<<<dim3((unsigned)G, COL_MAX / 64), 64 * FIN_SEG, 0, s>>>(a, out);
   return hipGetLastError();
 }
 
