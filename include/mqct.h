@@ -447,21 +447,21 @@ mqct_status mqct_adjoint(mqct_context* ctx, const mqct_batch_desc* batch, int32_
  *                          covering N) on a copy of up to 2048 of its
  *                          trajectories and keeps the fastest for the context;
  *                          0: the per-trajectory schedule's shape throughout.
- *                          The autotuner also times split-row shapes (4 or 8
- *                          waves that each hold all rows and stream a share of
- *                          the stored rows) against that choice on 32
+ *                          The autotuner also times shared-stream shapes (a
+ *                          thread per row, 4 or 8 waves that share out the
+ *                          stored rows) against that choice on 32
  *                          trajectories; if one wins, the class switches to it
  *                          once its active count falls to twice the number of
  *                          compute units (the latency-bound tail of a batch).
  *   MQCT_OPT_CHUNK         step launches per replay (1..4096, default 16).
  *   MQCT_OPT_RESET_TUNING  forget the shapes chosen so far (value ignored).
  *   MQCT_OPT_TAIL          1 (default): use the tuned tail shape; 0: never switch;
- *                          2: run every class on its widest split-row shape from
+ *                          2: run every class on its widest shared-stream shape from
  *                          the first step (for testing that form).
  *   MQCT_OPT_PER_LAUNCH    attempts (RK4 steps, DP5 attempts) of a trajectory per
  *                          step launch once a class is down to twice the number of
  *                          compute units (1..64; 1, the default: one per launch
- *                          throughout): a workgroup leaves its loop as soon as its
+ *                          throughout, as shared-stream shapes always do): a workgroup leaves its loop as soon as its
  *                          trajectory is done, so the value changes only the
  *                          number of launches, never a result.
  *   MQCT_OPT_COL_WORKSPACE the columns schedule's workspace cap in bytes (>= 0;

@@ -20,6 +20,8 @@ using namespace mqct;
 
 namespace {
 
+// Shared-stream form: most slice bytes per evaluation of the whole batch (mqct_run).
+constexpr double SHARED_MAX_BYTES = 320e6;
 // An adaptive batch on the default schedule sends the trajectories of a dense
 // system with at least this padded size and count to the binned schedule.
 constexpr int SPLIT_MIN_NPAD = 512;
@@ -79,6 +81,7 @@ struct DevBuf {
 
 struct mqct_context {
   int device = 0;
+  int n_cu = 256;                  // compute units of the device
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::string err;
@@ -254,6 +257,10 @@ mqct_status mqct_create(int32_t device, void* hip_stream, mqct_context** out) {
   if (hipSetDevice(device) != hipSuccess) return MQCT_ERR_DEVICE;
   mqct_context* c = new mqct_context();
   c->device = device;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
+      cus > 0)
+    c->n_cu = cus;
   if (hip_stream) {
     c->stream = (hipStream_t)hip_stream;
   } else {
@@ -1173,8 +1180,19 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
                            dtype_bytes(sy.dtype);
         }
       }
+      // A small batch left to the library runs in the shared-stream form: at most two
+      // trajectories per compute unit, and so few slice bytes per evaluation that the
+      // caches' latency and not their bandwidth sets the time.  N = 49 FP64, 100 steps:
+      // 3.0 -> 1.56 ms at 64 trajectories, 3.6 -> 2.1 at 512, no gain at 768 (4.06 and
+      // 3.5) and 1024; N = 256: 537 MB per evaluation (256 dense trajectories) 11.5
+      // ms either way, 747 MB (N = 300 complex) 1.15 -> 1.26, 134 MB 16.5 -> 11.5.
+      double slices = 0.0;
+      for (int64_t q = ranges[d].first; q < ranges[d].second; ++q)
+        slices += 4.0 * (double)c->systems[c->h_traj[q].sys].dev.knot_stride * dtype_bytes(d);
+      const bool shared = bd->schedule == MQCT_SCHED_AUTO && n <= 2 * (int64_t)c->n_cu &&
+                          slices <= SHARED_MAX_BYTES;
       hipError_t e = launch_rk4_gemv(c->d_systems, (const TrajIn*)c->traj.p + ranges[d].first, n,
-                                     d_a0, out, d, max_npad[d], c->stream, &c->prof);
+                                     d_a0, out, d, max_npad[d], c->stream, &c->prof, shared);
       if (e == hipErrorInvalidValue)
         return fail(c, MQCT_ERR_UNSUPPORTED, "run: N too large for the per-trajectory schedule");
       if (e != hipSuccess) return hip_fail(c, e, "run: launch");
@@ -1771,7 +1789,7 @@ const char* mqct_tuning_report(mqct_context* c) {
     if (en.tail_shape >= 0) {
       const QKernelSet& kt = queue_kernels(en.dtype)[en.tail_shape];
       snprintf(buf, sizeof buf, "{\"block\": %d, \"rows_per_lane\": %d, \"split_waves\": %d}",
-               kt.block, kt.rpt * (en.dtype == C128 ? 1 : 2), kt.split_waves);
+               kt.block, 1, kt.shared_form ? kt.block / 64 : 0);
       r += buf;
     } else {
       r += "null";
@@ -1781,7 +1799,9 @@ const char* mqct_tuning_report(mqct_context* c) {
       const QKernelSet& kj = queue_kernels(en.dtype)[en.tail_ms[j].first];
       snprintf(buf, sizeof buf,
                "%s{\"block\": %d, \"rows_per_lane\": %d, \"split_waves\": %d, \"ms\": %.6g}",
-               j ? ", " : "", kj.block, kj.rpt * (en.dtype == C128 ? 1 : 2), kj.split_waves,
+               j ? ", " : "", kj.block,
+               kj.shared_form ? 1 : kj.rpt * (en.dtype == C128 ? 1 : 2),
+               kj.shared_form ? kj.block / 64 : 0,
                en.tail_ms[j].second);
       r += buf;
     }

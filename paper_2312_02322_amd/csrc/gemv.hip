@@ -1,6 +1,6 @@
 // Fixed-step RK4 propagation with one workgroup per trajectory and the whole
 // step loop inside the kernel (the right-hand side is rhs.h).
-#include "rhs.h"
+#include "shared.h"
 
 #include <math.h>
 
@@ -9,7 +9,6 @@ namespace mqct {
 namespace {
 
 using namespace rhs;
-
 template <int DT, int BLOCK, int RPT>
 struct Kern : Rhs<DT, BLOCK, RPT> {
   using Base = Rhs<DT, BLOCK, RPT>;
@@ -118,6 +117,34 @@ rk4_gemv_kernel(const DevSystem* __restrict__ systems, const TrajIn* __restrict_
   Kern<DT, BLOCK, RPT>::run_rk4(sy, tj, a0_all, out, lds);
 }
 
+// The same in the shared-stream form (shared.h), for batches of at most two
+// trajectories per compute unit (two workgroups per unit: at most 256 registers).
+template <int DT, int BLOCK>
+__global__ void __launch_bounds__(BLOCK, 2)
+rk4_shared_kernel(const DevSystem* __restrict__ systems, const TrajIn* __restrict__ trajs,
+                  const double* __restrict__ a0_all, TrajOut out, int max_npad) {
+  using K = shared::SK<DT, BLOCK>;
+  const TrajIn tj = trajs[blockIdx.x];
+  const DevSystem sy = systems[tj.sys];
+  typename K::Own o;
+  K::setup(o, sy, max_npad);
+  K::run_rk4(o, sy, tj, a0_all, out);
+}
+
+template <int DT, int BLOCK>
+hipError_t launch_shared(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
+                         const double* d_a0, TrajOut out, int max_npad, hipStream_t s) {
+  const size_t lds = shared::lds_bytes(max_npad, DT == C64 || DT == R32, BLOCK, Tr<DT>::VEC);
+  auto kern = rk4_shared_kernel<DT, BLOCK>;
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  kern<<<(unsigned)n_traj, BLOCK, lds, s>>>(d_systems, d_traj, d_a0, out, max_npad);
+  return hipGetLastError();
+}
+
 template <int DT, int BLOCK, int RPT>
 hipError_t launch_one(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                       const double* d_a0, TrajOut out, int max_npad, hipStream_t s) {
@@ -140,8 +167,15 @@ hipError_t launch_one(const DevSystem* d_systems, const TrajIn* d_traj, int64_t 
 
 template <int DT>
 hipError_t launch_dt(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
-                     const double* d_a0, TrajOut out, int max_npad, hipStream_t s) {
+                     const double* d_a0, TrajOut out, int max_npad, bool shared_form,
+                     hipStream_t s) {
   const int groups = max_npad / Tr<DT>::VEC;
+  if (shared_form) {
+    if (shared::fits(max_npad, Tr<DT>::VEC, 256))
+      return launch_shared<DT, 256>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
+    if (shared::fits(max_npad, Tr<DT>::VEC, 512))
+      return launch_shared<DT, 512>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
+  }
   if (groups <= 64) return launch_one<DT, 64, 1>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
   if (groups <= 128) return launch_one<DT, 128, 1>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
   if (groups <= 256) return launch_one<DT, 256, 1>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
@@ -156,26 +190,27 @@ hipError_t launch_dt(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n
 
 hipError_t launch_rk4_gemv_t(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                              const double* d_a0, TrajOut out, int dtype, int max_npad,
-                             hipStream_t s);
+                             bool shared_form, hipStream_t s);
 
 hipError_t launch_rk4_gemv(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                            const double* d_a0, TrajOut out, int dtype, int max_npad,
-                           hipStream_t s, Prof* prof) {
+                           hipStream_t s, Prof* prof, bool shared_form) {
   hipEvent_t e0 = prof ? prof->next() : nullptr, e1 = prof ? prof->next() : nullptr;
   prof_mark(prof, e0, s);
-  hipError_t r = launch_rk4_gemv_t(d_systems, d_traj, n_traj, d_a0, out, dtype, max_npad, s);
+  hipError_t r = launch_rk4_gemv_t(d_systems, d_traj, n_traj, d_a0, out, dtype, max_npad,
+                                   shared_form, s);
   prof_mark(prof, e1, s);
   return r;
 }
 
 hipError_t launch_rk4_gemv_t(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                              const double* d_a0, TrajOut out, int dtype, int max_npad,
-                             hipStream_t s) {
+                             bool shared_form, hipStream_t s) {
   switch (dtype) {
-    case C128: return launch_dt<C128>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
-    case C64: return launch_dt<C64>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
-    case R64: return launch_dt<R64>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
-    case R32: return launch_dt<R32>(d_systems, d_traj, n_traj, d_a0, out, max_npad, s);
+    case C128: return launch_dt<C128>(d_systems, d_traj, n_traj, d_a0, out, max_npad, shared_form, s);
+    case C64: return launch_dt<C64>(d_systems, d_traj, n_traj, d_a0, out, max_npad, shared_form, s);
+    case R64: return launch_dt<R64>(d_systems, d_traj, n_traj, d_a0, out, max_npad, shared_form, s);
+    case R32: return launch_dt<R32>(d_systems, d_traj, n_traj, d_a0, out, max_npad, shared_form, s);
   }
   return hipErrorInvalidValue;
 }

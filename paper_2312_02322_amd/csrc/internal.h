@@ -198,7 +198,7 @@ hipError_t launch_spline_prepare(const double* M_in, const double* R, int N, int
 // must use systems of the same dtype whose padded column count is <= max_npad.
 hipError_t launch_rk4_gemv(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                            const double* d_a0, TrajOut out, int dtype, int max_npad,
-                           hipStream_t s, Prof* prof = nullptr);
+                           hipStream_t s, Prof* prof = nullptr, bool shared_form = false);
 
 // Adaptive-step controls.
 struct DpCtl {
@@ -248,13 +248,13 @@ struct QArgs {
 // (null when the shape is not built for the storage type).
 struct QKernelSet {
   int block, rpt;
-  int split_waves;     // 0: rows shared out over the workgroup; W: split-row form with W waves
+  bool shared_form;    // shared-stream form (shared.h), else rows shared out over the workgroup
   const void* init[2];
   const void* step[2];
   const void* step_multi[2];   // up to QArgs::per_launch attempts per launch (the tail)
 };
 const QKernelSet* queue_kernels(int dtype);   // [QUEUE_SHAPES]
-constexpr int QUEUE_SHAPES = 17;
+constexpr int QUEUE_SHAPES = 13;
 
 struct QueueClass {
   int dtype, npad;
@@ -264,8 +264,8 @@ struct QueueClass {
 struct QueueOpts {
   bool graphs = true;  // replay chunks of step launches as HIP graphs
   bool tune = true;    // time the candidate workgroup shapes on the batch
-  int tail = 1;        // 1: switch to the tuned split-row shape once few trajectories remain;
-                       // 0: never; 2: run every class on a split-row shape (tests)
+  int tail = 1;        // 1: switch to the tuned shared-stream shape once few trajectories
+                       // remain; 0: never; 2: run every class on one (tests)
   int chunk = 16;      // step launches per replay
   int per_launch = 1;  // attempts of a trajectory per step launch once few are left
   int64_t col_ws = 0;  // columns schedule: workspace cap in bytes (0: 80 % of free memory)

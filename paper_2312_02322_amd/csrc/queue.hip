@@ -13,15 +13,15 @@
 //   bulk  the row-split shapes (64..512 threads, fewest rows per lane covering
 //         Npad, lanes within a factor two of the rows), timed after the batch's
 //         init on a copy of the state of up to TUNE_SAMPLE trajectories;
-//   tail  the split-row shapes (4 or 8 waves that each hold all rows and stream
-//         a share of the stored rows) and the bulk choice, timed on a copy of
-//         TAIL_SAMPLE trajectories -- few enough that each has the device to
-//         itself, as in the last trajectories of a batch.  If a split-row shape
-//         wins, the class switches to it once its active count drops to twice
-//         the number of compute units.
+//   tail  the shared-stream shapes (4 or 8 waves that share out the stored rows)
+//         and the bulk choice, timed on a copy of TAIL_SAMPLE trajectories -- few
+//         enough that each has a compute unit to itself, as in the last
+//         trajectories of a batch.  If a shared-stream shape wins, the class
+//         switches to it once its active count drops to twice the number of
+//         compute units.
 // Each candidate is timed in two passes of two step launches (results are not
 // written); the choices are kept for the context.
-#include "rhs.h"
+#include "shared.h"
 
 #include <algorithm>
 #include <map>
@@ -140,25 +140,31 @@ int default_shape(int dtype, int npad) {
 }
 
 size_t shape_lds(int dtype, int npad, int shape) {
-  return rhs::lds_bytes(npad, dtype_fp32(dtype), queue_kernels(dtype)[shape].split_waves);
+  const QKernelSet& k = queue_kernels(dtype)[shape];
+  return k.shared_form ? shared::lds_bytes(npad, dtype_fp32(dtype), k.block, vec_of(dtype))
+                       : rhs::lds_bytes(npad, dtype_fp32(dtype));
 }
 
-// Row-split shapes (split = false) or split-row shapes (split = true) with the
-// fewest rows per lane covering Npad, lanes within a factor two of the rows.
-std::vector<int> candidates(int dtype, int npad, int method, bool split) {
+// Row-split shapes (shared_form = false): the fewest rows per lane covering Npad, lanes
+// within a factor two of the rows.  Shared-stream shapes (shared_form = true): those
+// that hold the rows.
+std::vector<int> candidates(int dtype, int npad, int method, bool shared_form) {
   const QKernelSet* t = queue_kernels(dtype);
   const int g = npad / vec_of(dtype);
   const int need = std::max(g, 64);
   std::vector<int> c;
   for (int k = 0; k < QUEUE_SHAPES; ++k) {
-    if (!t[k].step[method] || (t[k].split_waves > 0) != split) continue;
+    if (!t[k].step[method] || t[k].shared_form != shared_form) continue;
     if (shape_lds(dtype, npad, k) > LDS_MAX) continue;
-    const int lanes = (split ? 64 : t[k].block) * t[k].rpt;
+    if (shared_form) {
+      if (shared::fits(npad, vec_of(dtype), t[k].block)) c.push_back(k);
+      continue;
+    }
+    const int lanes = t[k].block * t[k].rpt;
     bool minimal = true;   // fewest rows per lane for this workgroup size
     for (int j = 0; j < QUEUE_SHAPES; ++j)
-      if (j != k && t[j].step[method] && (t[j].split_waves > 0) == split &&
-          t[j].block == t[k].block && t[j].rpt < t[k].rpt &&
-          (split ? 64 : t[j].block) * t[j].rpt >= g)
+      if (j != k && t[j].step[method] && !t[j].shared_form && t[j].block == t[k].block &&
+          t[j].rpt < t[k].rpt && t[j].block * t[j].rpt >= g)
         minimal = false;
     if (lanes >= g && lanes < 2 * need && minimal) c.push_back(k);
   }
@@ -180,7 +186,7 @@ struct ClassRun {
   QueueClass c;
   QWS ws;
   int shape = -1;        // shape in use
-  int tail_shape = -1;   // split-row shape for the tail (-1: none)
+  int tail_shape = -1;   // shared-stream shape for the tail (-1: none)
   size_t entry = 0;      // its entry in the context's cache
   int count = 0;         // last active count read back
   int grid = 0;          // grid of the current graph / launches
@@ -347,7 +353,7 @@ hipError_t run_queue(const DevSystem* d_systems, const TrajIn* d_traj,
       for (size_t ci = 0; ci < tc.size(); ++ci) en.tail_ms.push_back({tc[ci], best[ci]});
     }
   }
-  // forced split-row form (tests): the widest split-row candidate throughout
+  // forced shared-stream form (tests): the widest candidate throughout
   if (opt.tail == 2)
     for (ClassRun& r : runs) {
       const std::vector<int> tc = candidates(r.c.dtype, r.c.npad, method, true);

@@ -23,6 +23,7 @@
 #pragma once
 
 #include "rhs.h"
+#include "shared.h"
 
 namespace mqct {
 namespace queue {
@@ -43,9 +44,20 @@ static __constant__ double QA[7][6] = {
 static __constant__ double QE[7] = {71.0 / 57600, 0.0, -71.0 / 16695, 71.0 / 1920,
                                     -17253.0 / 339200, 22.0 / 525, -1.0 / 40};
 
-template <int DT, int BLOCK, int RPT, bool SPLIT>
-struct QK : Rhs<DT, BLOCK, RPT, SPLIT> {
-  using Base = Rhs<DT, BLOCK, RPT, SPLIT>;
+// Stage coefficients as the shared-stream stepper meets them: row p holds those of
+// k_p in the stages p + 1, p + 2, ... 6.
+static __constant__ double QT[7][6] = {
+    {1.0 / 5, 3.0 / 40, 44.0 / 45, 19372.0 / 6561, 9017.0 / 3168, 35.0 / 384},
+    {9.0 / 40, -56.0 / 15, -25360.0 / 2187, -355.0 / 33, 0, 0},
+    {32.0 / 9, 64448.0 / 6561, 46732.0 / 5247, 500.0 / 1113, 0, 0},
+    {-212.0 / 729, 49.0 / 176, 125.0 / 192, 0, 0, 0},
+    {-5103.0 / 18656, -2187.0 / 6784, 0, 0, 0, 0},
+    {11.0 / 84, 0, 0, 0, 0, 0},
+    {0, 0, 0, 0, 0, 0}};
+
+template <int DT, int BLOCK, int RPT>
+struct QK : Rhs<DT, BLOCK, RPT> {
+  using Base = Rhs<DT, BLOCK, RPT>;
   using Base::NR;
   using Base::NW;
   using Base::row;
@@ -436,13 +448,179 @@ struct QK : Rhs<DT, BLOCK, RPT, SPLIT> {
   }
 };
 
-template <int DT, int BLOCK, int RPT, bool SPLIT, int METHOD>
+// (Contractions are off as in shared.h.)
+#pragma clang fp contract(off)
+
+// The steppers in the shared-stream form (shared.h): one attempt, the state as QK
+// leaves and expects it (of kst only k1 is kept between attempts).
+template <int DT, int BLOCK>
+struct QS : shared::SK<DT, BLOCK> {
+  using Base = shared::SK<DT, BLOCK>;
+  using Own = typename Base::Own;
+
+  __device__ static void finish(Own& o, const DevSystem& sy, const TrajIn& tj, const TrajOut& out,
+                                double2 a, const QState& s, bool rk4) {
+    Sums tot;
+    bool b2 = false;
+    Base::eval_at(o, sy, s.t, s.yc, a, tot, b2, (tj.flags & TRAJ_AT) != 0);
+    Base::write_out(o, tj, out, a, s.yc, s.theta, s.ptheta, s.t, s.steps, s.rejects, s.status,
+                    tot, s.E0, s.J0);
+    if (out.P && threadIdx.x == 0)
+      put_traj_state(out, tj, sy.N, s.t, rk4 ? tj.t0 : s.t, rk4 ? s.n_idx : 0, s.h, s.yc,
+                     s.theta, s.ptheta, s.E0, s.J0, s.R_exit, s.steps, s.rejects, s.attempts,
+                     s.status, (s.flags & Q_LASTREJ) ? MQCT_S_LAST_REJECTED : 0);
+  }
+
+  // As QK::step_rk4.
+  __device__ static void step_rk4(const QArgs& q, int i, Own& o, const DevSystem& sy,
+                                  const TrajIn& tj, QState& s) {
+    double2* amp = q.ws.amp + (int64_t)i * q.ws.npad;
+    double2 a = o.row ? amp[o.n] : make_double2(0.0, 0.0);
+    const double h = tj.dt;
+    Sums tot;
+    bool below = false;
+    double y = Base::pick(s.yc[0], s.yc[1], s.yc[2], s.yc[3]);
+    Base::rk4_step(o, sy, tj.t0 + (double)s.n_idx * h, h, a, y, tot, below,
+                   (tj.flags & TRAJ_AT) != 0, 4, false);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s.yc[k] = Base::lane_val(y, k);
+    s.steps += 1;
+    s.attempts += 1;
+    s.n_idx += 1;
+    s.t = tj.t0 + (double)s.n_idx * h;
+    if (below) s.status |= ST_BELOW_GRID;
+    if (Base::bad(tot, y)) {
+      s.status |= ST_NONFINITE;
+      s.flags |= Q_DONE;
+    }
+    if (s.n_idx - tj.step0 >= tj.n_steps) s.flags |= Q_DONE;
+    if (o.row) amp[o.n] = a;
+    if (s.flags & Q_DONE) finish(o, sy, tj, q.out, a, s, true);
+  }
+
+  // As QK::step_dp5.  Each thread accumulates its row's inputs of the stages still to
+  // come (Y[0] the next one's) and the error sum; lane l carries the classical
+  // component l mod 4 the same way.
+  __device__ static void step_dp5(const QArgs& q, int i, Own& o, const DevSystem& sy,
+                                  const TrajIn& tj, QState& s) {
+    const double rtol = q.ctl.rtol, atol = q.ctl.atol;
+    const double ncomp = 2.0 * sy.N + 6.0;
+    const bool at = (tj.flags & TRAJ_AT) != 0;
+    double2* amp = q.ws.amp + (int64_t)i * q.ws.npad;
+    double2* k1p = q.ws.kst + (int64_t)i * 8 * q.ws.npad;
+    double2 a = make_double2(0.0, 0.0), kd = a;
+    if (o.row) {
+      a = amp[o.n];
+      kd = k1p[o.n];
+    }
+    bool done = false;
+    if (s.flags & Q_FINISH) {
+      s.flags &= ~Q_FINISH;
+      done = true;
+    } else {
+      const double h = s.h;
+      const double ts[shared::NPH] = {s.t + QC[1] * h, s.t + QC[2] * h, s.t + QC[3] * h,
+                                      s.t + QC[4] * h, s.t + QC[5] * h};
+      Base::phases(o, ts, 5);
+      const double ycl = Base::pick(s.yc[0], s.yc[1], s.yc[2], s.yc[3]);
+      double kl = Base::pick(s.kc1[0], s.kc1[1], s.kc1[2], s.kc1[3]);
+      double2 Y[6], st = a, err = make_double2(QE[0] * kd.x, QE[0] * kd.y);
+      double Yl[6], sl = ycl, errl = QE[0] * kl;
+#pragma unroll
+      for (int m = 0; m < 6; ++m) {
+        const double c = h * QT[0][m];
+        Y[m] = make_double2(fma(c, kd.x, a.x), fma(c, kd.y, a.y));
+        Yl[m] = fma(c, kl, ycl);
+      }
+      Sums tot{};
+      bool below = false;
+      for (int p = 1; p < 7; ++p) {
+        double c[5];
+#pragma unroll
+        for (int m = 0; m < 5; ++m) c[m] = h * QT[p][m];
+        const double ce = QE[p];
+        st = Y[0];
+        sl = Yl[0];
+        const double R = Base::lane_val(sl, 0), PR = Base::lane_val(sl, 2),
+                     PPhi = Base::lane_val(sl, 3);
+        double om;
+        kd = Base::eval(o, sy, min(p - 1, 4), R, PPhi, st, tot, below, om, at, false);
+        kl = Base::classical_rhs(o, R, PR, PPhi, om, tot);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+          Y[m] = make_double2(fma(c[m], kd.x, Y[m + 1].x), fma(c[m], kd.y, Y[m + 1].y));
+          Yl[m] = fma(c[m], kl, Yl[m + 1]);
+        }
+        err = make_double2(fma(ce, kd.x, err.x), fma(ce, kd.y, err.y));
+        errl = fma(ce, kl, errl);
+      }
+      // st, sl: the fifth-order solution; kd, kl: k_7.  Scaled RMS error.
+      double e2[1] = {0.0};
+      if (o.row) {
+        const double ex = err.x * h, ey = err.y * h;
+        const double sx = atol + rtol * fmax(fabs(a.x), fabs(st.x));
+        const double sy_ = atol + rtol * fmax(fabs(a.y), fabs(st.y));
+        const double qx = ex / sx, qy = ey / sy_;
+        e2[0] = fma(qx, qx, qy * qy);
+      }
+      double el = errl * h / (atol + rtol * fmax(fabs(ycl), fabs(sl)));
+      el *= el;
+      const double ecl = ((Base::lane_val(el, 0) + Base::lane_val(el, 1)) + Base::lane_val(el, 2)) +
+                         Base::lane_val(el, 3);
+      Base::template reduce<1>(o, e2);
+      const double en = uni(sqrt((e2[0] + ecl) / ncomp));
+      if (below) s.status |= ST_BELOW_GRID;
+      s.attempts += 1;
+      if (!isfinite(en)) {
+        s.status |= ST_NONFINITE;
+        done = true;
+      } else if (en <= 1.0) {
+        s.t += h;
+        a = st;
+        if (o.row) {
+          amp[o.n] = st;
+          k1p[o.n] = kd;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          s.yc[k] = Base::lane_val(sl, k);
+          s.kc1[k] = Base::lane_val(kl, k);
+        }
+        s.steps += 1;
+        double fac = en == 0.0 ? 5.0 : fmin(5.0, fmax(0.2, 0.9 * pow(en, -0.2)));
+        if (s.flags & Q_LASTREJ) fac = fmin(1.0, fac);
+        s.flags &= ~Q_LASTREJ;
+        if (s.yc[0] >= s.R_exit && s.yc[2] > 0.0) {
+          s.status |= ST_EXITED;
+          done = true;
+        } else {
+          s.h = uni(h * fac);
+        }
+      } else {
+        s.rejects += 1;
+        s.h = uni(h * fmax(0.2, 0.9 * pow(en, -0.2)));
+        s.flags |= Q_LASTREJ;
+      }
+      if (!done && s.h < q.ctl.h_min) { s.status |= ST_STEP_UNDERFLOW; done = true; }
+      if (!done && s.steps >= q.ctl.max_steps) { s.status |= ST_MAX_STEPS; done = true; }
+      if (!done && s.attempts >= q.max_attempts) { s.status |= ST_MAX_STEPS; done = true; }
+    }
+    if (done) {
+      s.flags |= Q_DONE;
+      finish(o, sy, tj, q.out, a, s, false);
+    }
+  }
+};
+
+#pragma clang fp contract(fast)
+
+template <int DT, int BLOCK, int RPT, int METHOD>
 __global__ void __launch_bounds__(BLOCK) q_init(QArgs q) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int i = blockIdx.x;
   Lds<DT> lds(smem, q.ws.npad);
-  if (METHOD == 0) QK<DT, BLOCK, RPT, SPLIT>::init_rk4(q, i, lds);
-  else QK<DT, BLOCK, RPT, SPLIT>::init_dp5(q, i, lds);
+  if (METHOD == 0) QK<DT, BLOCK, RPT>::init_rk4(q, i, lds);
+  else QK<DT, BLOCK, RPT>::init_dp5(q, i, lds);
   if (threadIdx.x == 0) q.ws.list[i] = i;
   if (i == 0 && threadIdx.x == 0) *q.ws.count = q.ws.n;
 }
@@ -455,7 +633,7 @@ __global__ void __launch_bounds__(BLOCK) q_init(QArgs q) {
 // is taken from one workgroup vote, so all waves leave together; each attempt
 // reads back only the rows its own threads wrote, and its LDS areas are separated
 // from the next attempt's writes by the barriers of the stage evaluations.
-template <int DT, int BLOCK, int RPT, bool SPLIT, int METHOD, bool MULTI>
+template <int DT, int BLOCK, int RPT, int METHOD, bool MULTI>
 __global__ void __launch_bounds__(BLOCK) q_step(QArgs q) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int cnt = *q.ws.count;
@@ -466,46 +644,65 @@ __global__ void __launch_bounds__(BLOCK) q_step(QArgs q) {
   Lds<DT> lds(smem, q.ws.npad);
   const int na = MULTI ? q.per_launch : 1;
   for (int a = 0; a < na; ++a) {
-    if (METHOD == 0) QK<DT, BLOCK, RPT, SPLIT>::step_rk4(q, i, s, lds);
-    else QK<DT, BLOCK, RPT, SPLIT>::step_dp5(q, i, s, lds);
+    if (METHOD == 0) QK<DT, BLOCK, RPT>::step_rk4(q, i, s, lds);
+    else QK<DT, BLOCK, RPT>::step_dp5(q, i, s, lds);
     if (!MULTI || __syncthreads_or((s.flags & Q_DONE) != 0)) break;
   }
   if (threadIdx.x == 0) q.ws.st[i] = s;
 }
 
-// Workgroup shapes (threads, 16-byte row groups per lane, split-row form) the
-// schedule can use: row-split 0..10, split-row 11..16.
+// One attempt in the shared-stream form.
+template <int DT, int BLOCK, int METHOD>
+__global__ void __launch_bounds__(BLOCK, 2) q_step_shared(QArgs q) {
+  const int cnt = *q.ws.count;
+  if ((int)blockIdx.x >= cnt) return;
+  const int i = q.ws.list[blockIdx.x];
+  QState s = q.ws.st[i];
+  if (s.flags & Q_DONE) return;
+  using K = QS<DT, BLOCK>;
+  const TrajIn tj = q.ws.traj[i];
+  const DevSystem sy = q.systems[tj.sys];
+  typename K::Own o;
+  K::setup(o, sy, q.ws.npad);
+  if (METHOD == 0) K::step_rk4(q, i, o, sy, tj, s);
+  else K::step_dp5(q, i, o, sy, tj, s);
+  if (threadIdx.x == 0) q.ws.st[i] = s;
+}
+
+// Workgroup shapes (threads, 16-byte row groups per lane) the schedule can use:
+// row-split 0..10, shared-stream 11 and 12.
 constexpr int QSHAPES = QUEUE_SHAPES;
 __host__ __device__ constexpr int qshape_block(int k) {
-  return k < 2 ? 64 : k < 4 ? 128 : k < 7 ? 256 : k < 11 ? 512 : k < 14 ? 256 : 512;
+  return k < 2 ? 64 : k < 4 ? 128 : k < 7 ? 256 : k < 11 ? 512 : k == 11 ? 256 : 512;
 }
 __host__ __device__ constexpr int qshape_rpt(int k) {
   return k == 0 ? 1 : k == 1 ? 2 : k == 2 ? 1 : k == 3 ? 2 : k == 4 ? 1 : k == 5 ? 2
-       : k == 6 ? 4 : k == 7 ? 1 : k == 8 ? 2 : k == 9 ? 4 : k == 10 ? 8
-       : k == 11 || k == 14 ? 1 : k == 12 || k == 15 ? 2 : 4;
+       : k == 6 ? 4 : k == 7 ? 1 : k == 8 ? 2 : k == 9 ? 4 : k == 10 ? 8 : 1;
 }
-__host__ __device__ constexpr bool qshape_split(int k) { return k >= 11; }
+__host__ __device__ constexpr bool qshape_shared(int k) { return k >= 11; }
 
 template <int DT, int K>
 void fill_one(QKernelSet& ks) {
   constexpr int BL = qshape_block(K), RP = qshape_rpt(K);
-  constexpr bool SP = qshape_split(K);
   ks.block = BL;
   ks.rpt = RP;
-  ks.split_waves = SP ? BL / 64 : 0;
-  // rows per workgroup (per wave for the split-row form) beyond the largest
-  // supported column count are not built
-  if constexpr ((SP ? 64 : BL) * RP * Tr<DT>::VEC > 4096) {
-    ks.init[0] = ks.init[1] = ks.step[0] = ks.step[1] = ks.step_multi[0] = ks.step_multi[1] =
-        nullptr;
-    return;
-  } else {
-    ks.init[0] = (const void*)q_init<DT, BL, RP, SP, 0>;
-    ks.init[1] = (const void*)q_init<DT, BL, RP, SP, 1>;
-    ks.step[0] = (const void*)q_step<DT, BL, RP, SP, 0, false>;
-    ks.step[1] = (const void*)q_step<DT, BL, RP, SP, 1, false>;
-    ks.step_multi[0] = (const void*)q_step<DT, BL, RP, SP, 0, true>;
-    ks.step_multi[1] = (const void*)q_step<DT, BL, RP, SP, 1, true>;
+  ks.shared_form = qshape_shared(K);
+  ks.init[0] = ks.init[1] = ks.step[0] = ks.step[1] = ks.step_multi[0] = ks.step_multi[1] =
+      nullptr;
+  if constexpr (qshape_shared(K)) {
+    // a class is initialised with its row-split shape; one attempt per launch always
+    // (a loop of attempts would hold more registers than two workgroups per compute
+    // unit have)
+    ks.step[0] = ks.step_multi[0] = (const void*)q_step_shared<DT, BL, 0>;
+    ks.step[1] = ks.step_multi[1] = (const void*)q_step_shared<DT, BL, 1>;
+  } else if constexpr (BL * RP * Tr<DT>::VEC <= 4096) {
+    // (rows per workgroup beyond the largest supported column count are not built)
+    ks.init[0] = (const void*)q_init<DT, BL, RP, 0>;
+    ks.init[1] = (const void*)q_init<DT, BL, RP, 1>;
+    ks.step[0] = (const void*)q_step<DT, BL, RP, 0, false>;
+    ks.step[1] = (const void*)q_step<DT, BL, RP, 1, false>;
+    ks.step_multi[0] = (const void*)q_step<DT, BL, RP, 0, true>;
+    ks.step_multi[1] = (const void*)q_step<DT, BL, RP, 1, true>;
   }
 }
 

@@ -106,11 +106,9 @@ __device__ __forceinline__ void elem(F2& u, F2& v, F s0r, F s0i, F s1r, F s1i, F
 //   c64   [Npad] double2 (aliases c on the FP64 path)
 //   red0  [16][8] doubles, red1 [16][8] doubles  (two reduction areas)
 //   kcl   [8][4] doubles                        (classical stage derivatives of DP5)
-//   part  [W][Npad] double4                     (split-row form only: each wave's
-//                                                partial (u, v) before they are summed)
-__host__ __device__ inline size_t lds_bytes(int npad, bool fp32, int split_waves = 0) {
+__host__ __device__ inline size_t lds_bytes(int npad, bool fp32) {
   size_t c = fp32 ? (((size_t)npad * 8 + 15) & ~(size_t)15) : 0;
-  return c + (size_t)npad * 16 + 2 * 16 * 8 * 8 + 8 * 4 * 8 + (size_t)split_waves * npad * 32;
+  return c + (size_t)npad * 16 + 2 * 16 * 8 * 8 + 8 * 4 * 8;
 }
 
 template <int DT>
@@ -120,7 +118,6 @@ struct Lds {
   double* red0;
   double* red1;
   double* kcl;
-  double4* part;
   __device__ Lds(unsigned char* smem, int npad) {
     constexpr bool fp32 = (DT == C64 || DT == R32);
     c = (typename Tr<DT>::CS*)smem;
@@ -128,19 +125,13 @@ struct Lds {
     red0 = (double*)(c64 + npad);
     red1 = red0 + 16 * 8;
     kcl = red1 + 16 * 8;
-    part = (double4*)(kcl + 8 * 4);
   }
 };
 
-// Right-hand side evaluated by one workgroup.  Row-split form (SPLIT = false):
-// the BLOCK threads share out the output rows and every thread streams all N
-// stored rows.  Split-row form (SPLIT = true): every wave holds all output rows
-// (64 lanes x RPT groups) and streams only its 1/W share of the stored rows;
-// the W partial sums meet in LDS and are added in a fixed order, so every wave
-// ends with the same u and v and carries the trajectory's state redundantly.
-// The split form shortens the dependent chain of loads W times: it serves
-// trajectories that run alone on the device (latency-bound tails).
-template <int DT, int BLOCK, int RPT, bool SPLIT = false>
+// Right-hand side evaluated by one workgroup: the BLOCK threads share out the
+// output rows and every thread streams all N stored rows.  (Trajectories that run
+// alone on the device use the shared-stream form of shared.h.)
+template <int DT, int BLOCK, int RPT>
 struct Rhs {
   using T = Tr<DT>;
   using S = typename T::S;
@@ -152,9 +143,8 @@ struct Rhs {
   static constexpr bool FP32 = (DT == C64 || DT == R32);
   static constexpr bool CPLX = T::CPLX;
   static constexpr int NCOMP = CPLX ? 2 : 1;
-  // stored rows in flight per lane (the split-row form streams fewer rows per
-  // wave and is latency-bound, so it keeps more in flight)
-  static constexpr int UNR = SPLIT ? (RPT >= 8 ? 1 : 8 / RPT) : (RPT >= 4 ? 1 : 4 / RPT);
+  // stored rows in flight per lane
+  static constexpr int UNR = RPT >= 4 ? 1 : 4 / RPT;
   // sparse real tables: slots per batch whose row indices and table elements are
   // all requested before the first gather of c (their elements are small enough
   // to hold a batch in registers)
@@ -164,21 +154,14 @@ struct Rhs {
   using F = typename std::conditional<FP32, float, double>::type;
   using F2 = typename std::conditional<FP32, float2, double2>::type;
 
-  static constexpr int ROWW = SPLIT ? 64 : BLOCK;   // threads that share out the rows
-  __device__ static int rlane() { return SPLIT ? (int)(threadIdx.x & 63) : (int)threadIdx.x; }
+  static constexpr int ROWW = BLOCK;   // threads that share out the rows
+  __device__ static int rlane() { return (int)threadIdx.x; }
   __device__ static int row(int r) { return (rlane() + (r / VEC) * ROWW) * VEC + (r % VEC); }
 
-  // Sum NV values over the trajectory's rows, identical in every lane.  The
-  // row-split form reduces over the workgroup; in the split-row form each wave
-  // holds all rows, so a wave reduction suffices.  Both end with a barrier.
+  // Sum NV values over the workgroup's rows, identical in every lane.
   template <int NV>
   __device__ static void reduce(double (&v)[NV], double* red) {
-    if constexpr (SPLIT) {
-      wave_sum<NV>(v);
-      __syncthreads();
-    } else {
-      block_sum<NV, NW>(v, red);
-    }
+    block_sum<NV, NW>(v, red);
   }
 
   // The VEC elements of one 16-byte load, as (re, im) pairs.
@@ -242,12 +225,7 @@ struct Rhs {
     // ell_w slots of the sparse ones (slot q of column n holds stored row
     // col[q][n], so c is gathered per element instead of broadcast)
     const int nst = sy.ell_w > 0 ? sy.ell_w : N;
-    int mb = 0, me = nst;
-    if constexpr (SPLIT) {
-      const int w = threadIdx.x >> 6;
-      mb = (nst * w) / NW;
-      me = (nst * (w + 1)) / NW;
-    }
+    const int mb = 0, me = nst;
     const auto rcol = slice_rsrc(sy.ell_col, (uint32_t)((int64_t)nst * Npad * 4));
     auto stream = [&](auto sparse) {
       constexpr bool ELL = decltype(sparse)::value;
@@ -362,29 +340,6 @@ struct Rhs {
     };
     if (sy.ell_w > 0) stream(std::true_type{});
     else stream(std::false_type{});
-
-    if constexpr (SPLIT) {
-      // every wave's partial sums of all rows, added in wave order
-      const int w = threadIdx.x >> 6;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int n = row(r);
-        if (n < Npad) lds.part[w * Npad + n] = make_double4(U[r].x, U[r].y, V[r].x, V[r].y);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int n = row(r);
-        if (n >= Npad) continue;
-        double4 acc = lds.part[n];
-        for (int q = 1; q < NW; ++q) {
-          const double4 p = lds.part[q * Npad + n];
-          acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
-        }
-        U[r] = make_double2(acc.x, acc.y);
-        V[r] = make_double2(acc.z, acc.w);
-      }
-    }
 
     // epilogue.  J_x couples only channels of equal energy, so
     // J_x a = e^{iE_n t} (J_x c) row by row, and with y = e^{iE t} u:
