@@ -449,7 +449,7 @@ mqct_status mqct_adjoint(mqct_context* ctx, const mqct_batch_desc* batch, int32_
  *                          0: the per-trajectory schedule's shape throughout.
  *                          The autotuner also times shared-stream shapes (a
  *                          thread per row, 4 or 8 waves that share out the
- *                          stored rows) against that choice on 32
+ *                          stored rows) against that choice on up to 320
  *                          trajectories; if one wins, the class switches to it
  *                          once its active count falls to twice the number of
  *                          compute units (the latency-bound tail of a batch).

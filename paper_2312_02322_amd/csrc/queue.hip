@@ -14,9 +14,12 @@
 //         Npad, lanes within a factor two of the rows), timed after the batch's
 //         init on a copy of the state of up to TUNE_SAMPLE trajectories;
 //   tail  the shared-stream shapes (4 or 8 waves that share out the stored rows)
-//         and the bulk choice, timed on a copy of TAIL_SAMPLE trajectories -- few
-//         enough that each has a compute unit to itself, as in the last
-//         trajectories of a batch.  If a shared-stream shape wins, the class
+//         and the bulk choice, timed on a copy of TAIL_SAMPLE trajectories -- between
+//         one and two per compute unit, as the tail starts: a shape of which only one
+//         workgroup fits a unit is two rounds there.  (On 32 trajectories the 512-
+//         thread shape won by 43 to 46 us per attempt at N = 256 and then took 86 of
+//         the 59 us that 321 trajectories need: 6.6 s instead of 5.4 for the uneven
+//         workload.)  If a shared-stream shape wins, the class
 //         switches to it once its active count drops to twice the number of
 //         compute units.
 // Each candidate is timed in two passes of two step launches (results are not
@@ -46,7 +49,7 @@ const QKernelSet* queue_kernels(int dtype) {
 namespace {
 
 constexpr int64_t TUNE_SAMPLE = 2048;
-constexpr int64_t TAIL_SAMPLE = 32;
+constexpr int64_t TAIL_SAMPLE = 320;
 constexpr size_t LDS_MAX = 160 * 1024;
 constexpr int CT = 1024;   // threads of the compaction kernel
 
