@@ -452,7 +452,8 @@ mqct_status mqct_adjoint(mqct_context* ctx, const mqct_batch_desc* batch, int32_
  *                          stored rows) against that choice on up to 320
  *                          trajectories; if one wins, the class switches to it
  *                          once its active count falls to twice the number of
- *                          compute units (the latency-bound tail of a batch).
+ *                          compute units (the latency-bound tail of a batch;
+ *                          adaptive classes of at most 16 columns never switch).
  *   MQCT_OPT_CHUNK         step launches per replay (1..4096, default 16).
  *   MQCT_OPT_RESET_TUNING  forget the shapes chosen so far (value ignored).
  *   MQCT_OPT_TAIL          1 (default): use the tuned tail shape; 0: never switch;

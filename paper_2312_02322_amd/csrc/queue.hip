@@ -21,7 +21,7 @@
 //         the 59 us that 321 trajectories need: 6.6 s instead of 5.4 for the uneven
 //         workload.)  If a shared-stream shape wins, the class
 //         switches to it once its active count drops to twice the number of
-//         compute units.
+//         compute units.  (The smallest adaptive classes do not: TAIL_MIN_NPAD.)
 // Each candidate is timed in two passes of two step launches (results are not
 // written); the choices are kept for the context.
 #include "shared.h"
@@ -50,6 +50,13 @@ namespace {
 
 constexpr int64_t TUNE_SAMPLE = 2048;
 constexpr int64_t TAIL_SAMPLE = 320;
+// Adaptive classes of at most this many columns keep their bulk shape to the end.  Whole
+// collisions of a rotor with so few channels (N = 9 and 16, 150 to 2000 cm^-1) carry a
+// change in the order of a sum from 1e-16 to between 2e-9 and 3e-7 of the final state, so
+// the last trajectories of a batch are stepped as the others are, at 1.6 to 1.8 times the
+// shared-stream form's time (66 trajectories, N = 16: 6.8 and 4.2 ms).  N = 81 and 256
+// carry it to 1e-10 at most.
+constexpr int TAIL_MIN_NPAD = 17;
 constexpr size_t LDS_MAX = 160 * 1024;
 constexpr int CT = 1024;   // threads of the compaction kernel
 
@@ -345,7 +352,7 @@ hipError_t run_queue(const DevSystem* d_systems, const TrajIn* d_traj,
       for (size_t ci = 0; ci < cand.size(); ++ci) en.ms.push_back({cand[ci], best[ci]});
     }
     std::vector<int> tc = candidates(r.c.dtype, r.c.npad, method, true);
-    if (!tc.empty()) {
+    if (!tc.empty() && (method == 0 || r.c.npad >= TAIL_MIN_NPAD)) {
       tc.push_back(r.shape);
       if ((e = time_shapes(r, std::min(r.c.n, TAIL_SAMPLE), tc, best)) != hipSuccess) return e;
       size_t bi = 0;
