@@ -149,6 +149,13 @@ __device__ __forceinline__ void stage_setup(const BinWS& ws, const DevSystem& sy
   if (sp.below && count_below) ws.status[b] |= ST_BELOW_GRID;
 }
 
+// e^{-iEt} a from (cos Et, sin Et), with its roundings written out: the step that a
+// resumed run prepares on its own and the one prepared by the combine before it start
+// from the same bits.
+__device__ __forceinline__ double2 rotate(double cs, double sn, double2 a) {
+  return make_double2(fma(cs, a.x, sn * a.y), fma(cs, a.y, -(sn * a.x)));
+}
+
 // Element n of the two real columns of c in the table precision (KR = 2 Npad
 // reals for complex tables, Npad for real ones): complex tables take
 // (Re c_n, -Im c_n) and (Im c_n, Re c_n) at reals 2n, 2n+1; real tables take
@@ -201,7 +208,7 @@ bin_prep(BinWS ws, const DevSystem* __restrict__ systems, int64_t j, int st, int
       ws.cur[o] = a;
       double sn, cs;
       sincos(sy.E[n] * t, &sn, &cs);
-      c = make_double2(cs * a.x + sn * a.y, cs * a.y - sn * a.x);
+      c = rotate(cs, sn, a);
     }
     put_cols<S, CPLX>(ws, b, Npad, n, c);
   }
@@ -521,7 +528,7 @@ bin_combine(BinWS ws, const DevSystem* __restrict__ systems, int64_t j, int st, 
     const double2 cur = ws.cur[(int64_t)b * Npad + n];
     double sn, cs;
     sincos(sy.E[n] * t, &sn, &cs);
-    cb[n] = make_double2(cs * cur.x + sn * cur.y, cs * cur.y - sn * cur.x);
+    cb[n] = rotate(cs, sn, cur);
     if constexpr (LDSC) ph[n] = make_double2(cs, sn);
     const double pn = cur.x * cur.x + cur.y * cur.y;
     sums[3] += sy.E[n] * pn;
@@ -594,8 +601,7 @@ bin_combine(BinWS ws, const DevSystem* __restrict__ systems, int64_t j, int st, 
         ws.cur[o] = curn;
         double snn = sn, csn = cs;
         if (!same_t) sincos(sy.E[n] * tn, &snn, &csn);
-        put_cols<S, CPLX>(ws, b, Npad, n, make_double2(csn * curn.x + snn * curn.y,
-                                                       csn * curn.y - snn * curn.x));
+        put_cols<S, CPLX>(ws, b, Npad, n, rotate(csn, snn, curn));
       }
     }
   }
@@ -817,7 +823,7 @@ d5_combine(BinWS ws, D5WS d, const DevSystem* __restrict__ systems, int mode, in
     const double2 cur = ws.cur[(int64_t)b * Npad + n];
     double sn, cs;
     sincos(sy.E[n] * t, &sn, &cs);
-    cb[n] = make_double2(cs * cur.x + sn * cur.y, cs * cur.y - sn * cur.x);
+    cb[n] = rotate(cs, sn, cur);
     const double pn = cur.x * cur.x + cur.y * cur.y;
     sums[3] += sy.E[n] * pn;
     sums[4] += pn;
