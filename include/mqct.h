@@ -71,7 +71,11 @@ enum {
 };
 /* batch schedules */
 enum {
-  MQCT_SCHED_AUTO = 0,        /* library chooses                                        */
+  MQCT_SCHED_AUTO = 0,        /* library chooses: GEMV for fixed steps, BINNED where a
+                                 single FP64 dense system has large tables or many
+                                 trajectories (by N, K and B alone), QUEUE for DP5
+                                 (with large dense systems' shares on BINNED), COLUMNS
+                                 for coordinate-list systems                         */
   MQCT_SCHED_GEMV = 1,        /* one workgroup per trajectory, step loop inside a kernel */
   MQCT_SCHED_BINNED = 2,      /* lockstep stages, trajectories binned by spline knot,
                                  table x amplitude-columns products on matrix cores;
@@ -375,7 +379,7 @@ mqct_status mqct_set_state(mqct_context* ctx, int64_t first, int64_t count,
  * beyond that fails with MQCT_ERR_ARG before any device work.  Fixed-step RK4 on
  * the per-trajectory schedule only (schedule MQCT_SCHED_AUTO or MQCT_SCHED_GEMV,
  * resume 0; otherwise MQCT_ERR_UNSUPPORTED); results must be device arrays
- * (mem = MQCT_MEM_DEVICE).  The results equal mqct_run's on that schedule; the
+ * (mem = MQCT_MEM_DEVICE).  The results equal mqct_run's on MQCT_SCHED_GEMV; the
  * state store is left as it was.  The call waits for the context stream before it
  * stages the records (synchronous host-to-device copies) and returns with the
  * propagation enqueued.  All calls on one GPU share the scratch array, so calls

@@ -22,6 +22,9 @@ namespace {
 
 // Shared-stream form: most slice bytes per evaluation of the whole batch (mqct_run).
 constexpr double SHARED_MAX_BYTES = 320e6;
+// Workspace of one binned pass of a fixed-step batch on the default schedule; a larger
+// batch runs in several.
+constexpr size_t AUTO_BINNED_WS = (size_t)1 << 30;
 // An adaptive batch on the default schedule sends the trajectories of a dense
 // system with at least this padded size and count to the binned schedule.
 constexpr int SPLIT_MIN_NPAD = 512;
@@ -149,6 +152,33 @@ mqct_status ensure(mqct_context* c, DevBuf& b, size_t bytes, const char* what) {
   HIP_TRY(c, dev_malloc(&b.p, want), what);
   b.cap = want;
   return MQCT_OK;
+}
+
+// Whether a fixed-step batch left to the library runs on the binned schedule: one
+// system, dense FP64 tables (binned FP32 products would add up in FP32, the
+// per-trajectory kernels add in FP64), and either
+//  - so much work that table traffic sets the time: per evaluation at least 1 GB of the
+//    slices that one workgroup per trajectory reads, and 3/4 K trajectories (a product
+//    reads each occupied knot once, at worst all K).  One evaluation, per-trajectory ->
+//    binned, complex tables: N = 969, K = 200, B = 1024 8.1 -> 1.2 ms; N = 256, K = 1000,
+//    B = 1024 687 -> 360 us; N = 160, K = 200, B = 1024 239 -> 101 us.  Below: N = 256,
+//    K = 1000, B = 256 (1.07 GB) 190 -> 217 us; N = 100, K = 200, B = 512 (0.34 GB)
+//    50 -> 48 us.  Slices of 1.2 MB, because lockstep ends with the longest trajectory:
+//    one alone takes 29 -> 40 us an evaluation at complex N = 160, 12 -> 25 at N = 49;
+//  - or a slice set so large that one workgroup walks it for longer than the lockstep
+//    stage's launches take and the few rows of a small batch leave the device idle:
+//    8 MB and at most 64 trajectories, or 24 MB.  K = 1000, each trajectory on knots of
+//    its own: real N = 512 (8.4 MB) B = 1 93 -> 55 us, B = 64 158 -> 118 us, B = 128
+//    186 -> 220; complex N = 640 (26 MB) B = 1 458 -> 103, B = 256 991 -> 941 us; below
+//    8 MB, real N = 400 (5.1 MB): B = 1 60 -> 48 us, B = 128 143 -> 154.
+// The step counts do not enter: a run in two calls takes the same route in both.
+bool auto_binned(const DevSystem& sy, const TrajIn* t, int64_t B) {
+  if ((sy.dtype != C128 && sy.dtype != R64) || sy.ell_w > 0 || sy.Npad > 4096) return false;
+  for (int64_t b = 0; b < B; ++b)
+    if (t[b].sys != t[0].sys || t[b].n_steps >= INT32_MAX) return false;
+  const double slices = 4.0 * (double)sy.knot_stride * dtype_bytes(sy.dtype);
+  return ((double)B * slices >= 1e9 && (double)B >= 0.75 * sy.K && slices >= 1.2e6) ||
+         (slices >= 8e6 && B <= 64) || slices >= 24e6;
 }
 
 mqct_status upload_systems(mqct_context* c) {
@@ -1108,6 +1138,27 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
   out.state = (mqct_traj_state*)c->st_rec.p;
   out.st_amp = (double2*)c->st_amp.p;
 
+  // fixed steps on the binned schedule: asked for, or the library's choice (without
+  // room for its workspace the per-trajectory schedule stands)
+  bool rk4_binned = binned && !dp5;
+  int64_t bin_n = B;      // trajectories per pass
+  if (rk4_binned) {
+    const DevSystem& hs = c->systems[c->h_traj[0].sys].dev;
+    const size_t wsb = binned_workspace_bytes((int)B, hs.Npad, hs.K, dtype_fp32(hs.dtype));
+    if ((st = ensure(c, c->binws, wsb, "run: binned workspace")) != MQCT_OK) return st;
+  } else if (bd->schedule == MQCT_SCHED_AUTO && !dp5 && !columns &&
+             auto_binned(c->systems[c->h_traj[0].sys].dev, c->h_traj, B)) {
+    const DevSystem& hs = c->systems[c->h_traj[0].sys].dev;
+    auto need = [&](int64_t n) { return binned_workspace_bytes((int)n, hs.Npad, hs.K, false); };
+    bin_n = std::min<int64_t>(B, 1 << 20);
+    while (bin_n > 64 && need(bin_n) > AUTO_BINNED_WS) bin_n = (bin_n + 1) / 2;
+    const std::string err = c->err;
+    rk4_binned = ensure(c, c->binws, need(bin_n), "run: binned workspace") == MQCT_OK;
+    if (!rk4_binned) {
+      c->err = err;
+      (void)hipGetLastError();
+    }
+  }
   if (columns) {
     const DevSystem& hs = c->systems[c->h_traj[0].sys].dev;
     const bool f32 = dtype_fp32(hs.dtype);
@@ -1159,15 +1210,16 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
     hipError_t e = run_binned_dp5(c->d_systems, hs, (const TrajIn*)c->traj.p, (int)B, d_a0, out,
                                   ctl, max_attempts, c->binws.p, c->stream, &c->prof);
     if (e != hipSuccess) return hip_fail(c, e, "run: binned DP5");
-  } else if (binned) {
+  } else if (rk4_binned) {
     const DevSystem& hs = c->systems[c->h_traj[0].sys].dev;
-    int64_t max_steps = 0;
-    for (int64_t b = 0; b < B; ++b) max_steps = std::max(max_steps, c->h_traj[b].n_steps);
-    const size_t wsb = binned_workspace_bytes((int)B, hs.Npad, hs.K, dtype_fp32(hs.dtype));
-    if ((st = ensure(c, c->binws, wsb, "run: binned workspace")) != MQCT_OK) return st;
-    hipError_t e = run_binned(c->d_systems, hs, (const TrajIn*)c->traj.p, (int)B, max_steps,
-                              d_a0, out, c->binws.p, c->stream, &c->prof);
-    if (e != hipSuccess) return hip_fail(c, e, "run: binned launch");
+    for (int64_t b0 = 0; b0 < B; b0 += bin_n) {
+      const int n = (int)std::min<int64_t>(bin_n, B - b0);
+      int64_t max_steps = 0;
+      for (int64_t b = b0; b < b0 + n; ++b) max_steps = std::max(max_steps, c->h_traj[b].n_steps);
+      hipError_t e = run_binned(c->d_systems, hs, (const TrajIn*)c->traj.p + b0, n, max_steps,
+                                d_a0, out, c->binws.p, c->stream, &c->prof);
+      if (e != hipSuccess) return hip_fail(c, e, "run: binned launch");
+    }
   } else if (!queue) {
     for (int d = 0; d < 4; ++d) {
       int64_t n = ranges[d].second - ranges[d].first;
