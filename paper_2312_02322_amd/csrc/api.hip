@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <map>
 #include <string>
 #include <thread>
@@ -1947,9 +1948,17 @@ namespace {
 // Validation and device set-up shared by the dense and the screened builds: the
 // (j1, j2, j) levels, terms sorted by lam, channels grouped by m, the work list
 // (per row, tiles of 256 channels of the row's m group), and one device
-// workspace holding them with the factor arrays.  On success *buf owns it.
+// workspace holding them with the factor arrays.  On success *buf owns it.  With early,
+// that is called once the arguments are known to be good: what it enqueues runs while the
+// host lays out the rest, whose uploads are then ordered on the stream and read `hold`
+// until the stream has been waited for.
+struct CouplingHold {
+  std::vector<int32_t> ints;
+  std::vector<double> vs;
+};
 mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const char* what,
-                           CouplingDev& dev, char** buf) {
+                           CouplingDev& dev, char** buf, CouplingHold& hold,
+                           const std::function<hipError_t(int, int, int)>& early = nullptr) {
   *buf = nullptr;
   if (!d) return fail(c, MQCT_ERR_ARG, "%s: null descriptor", what);
   const int N = d->N, T = d->T, K = d->K, n1 = d->n_rot1, bs = d->b_stride;
@@ -1994,11 +2003,16 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
                   "|lam1-lam2| <= lam <= lam1+lam2", what, t, LMAX);
     perm[t] = t;
   }
+  HIP_TRY(c, hipSetDevice(c->device), what);
+  hipError_t e = early ? early(N, T, K) : hipSuccess;
+  if (e == hipErrorInvalidValue)
+    return fail(c, MQCT_ERR_ARG, "%s: output too large for one launch", what);
+  if (e != hipSuccess) return hip_fail(c, e, what);
   // terms sorted by lam (kept from the first form of the fill kernel; the order of
   // the sums over t is then the same in every kernel)
   std::stable_sort(perm.begin(), perm.end(),
                    [&](int a, int b) { return d->lam[a] < d->lam[b]; });
-  std::vector<int32_t> ints;
+  std::vector<int32_t>& ints = hold.ints;
   auto put = [&](const int32_t* p, size_t n) {
     const size_t o = ints.size();
     ints.insert(ints.end(), p, p + n);
@@ -2006,7 +2020,8 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
   };
   std::vector<int32_t> tl1(T), tmu(T), tl2(T), tl(T);
   const int KP = (K + CPL_KNOT_CHUNK - 1) / CPL_KNOT_CHUNK * CPL_KNOT_CHUNK;
-  std::vector<double> vs((size_t)T * KP, 0.0);
+  std::vector<double>& vs = hold.vs;
+  vs.assign((size_t)T * KP, 0.0);
   int cg_lmax = 0, cg_jmax = 0;
   for (int t = 0; t < T; ++t) {
     const int u = perm[t];
@@ -2059,29 +2074,33 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
   if (ints.size() & 1) ints.push_back(0);      // the work list is read as int2
   const size_t o_wk = put(work.data(), work.size());
   const size_t ibytes = (ints.size() * 4 + 255) / 256 * 256;
-  const size_t n_b = (size_t)n1 * bs, n_v = (size_t)T * KP, n_lf = 256;
-  const size_t n_K = (size_t)T * n1 * n1, n_F = (size_t)T * nJ * nJ;
+  const int TP = (T + 1) & ~1;
+  const size_t n_b = ((size_t)n1 * bs + 1) & ~(size_t)1, n_v = (size_t)T * KP, n_lf = 256;
+  const size_t n_K = (size_t)TP * n1 * n1, n_F = (size_t)TP * nJ * nJ;
   const size_t n_cg = (size_t)(cg_jmax + 1) * (cg_jmax + 1) * (2 * cg_jmax + 1) * (cg_lmax + 1);
   const size_t total = ibytes + (n_b + n_v + n_lf + n_K + n_F + n_cg) * 8;
-  HIP_TRY(c, hipSetDevice(c->device), what);
   char* w = nullptr;
-  hipError_t e = dev_malloc((void**)&w, total);
-  if (e != hipSuccess) return hip_fail(c, e, what);
+  if ((e = dev_malloc((void**)&w, total)) != hipSuccess) return hip_fail(c, e, what);
   int32_t* di = (int32_t*)w;
   double* dd = (double*)(w + ibytes);
   double *db = dd, *dv = db + n_b, *dlf = dv + n_v, *dK = dlf + n_lf, *dF = dK + n_K,
          *dcg = dF + n_F;
-  if ((e = hipMemcpy(di, ints.data(), ints.size() * 4, hipMemcpyHostToDevice)) == hipSuccess &&
-      (e = hipMemcpy(db, d->b, n_b * 8, hipMemcpyHostToDevice)) == hipSuccess)
-    e = hipMemcpy(dv, vs.data(), n_v * 8, hipMemcpyHostToDevice);
+  auto up = [&](void* dst, const void* src, size_t bytes) {
+    return early ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream)
+                 : hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+  };
+  if ((e = up(di, ints.data(), ints.size() * 4)) == hipSuccess &&
+      (e = up(db, d->b, (size_t)n1 * bs * 8)) == hipSuccess)
+    e = up(dv, vs.data(), n_v * 8);
   if (e != hipSuccess) {
+    if (early) (void)hipStreamSynchronize(c->stream);
     hipFree(w);
     return hip_fail(c, e, what);
   }
   dev = CouplingDev{N, T, K, n1, nJ, bs, di + o_cJ, di + o_cr, di + o_cj, di + o_cm,
                     di + o_j1, di + o_j2, di + o_jj, di + o_rj, db, di + o_t1, di + o_tm,
                     di + o_t2, di + o_tl, di + o_tu, dv, dlf, dK, dF, di + o_cg, di + o_go,
-                    di + o_gl, (const int2*)(di + o_wk), n_work, KP, cg_jmax, cg_lmax, dcg};
+                    di + o_gl, (const int2*)(di + o_wk), n_work, TP, KP, cg_jmax, cg_lmax, dcg};
   *buf = w;
   return MQCT_OK;
 }
@@ -2094,10 +2113,27 @@ mqct_status mqct_coupling_build(mqct_context* c, const mqct_coupling_desc* d, do
   if (!M_out && !G_out) return fail(c, MQCT_ERR_ARG, "coupling_build: no output requested");
   CouplingDev dev;
   char* buf = nullptr;
-  mqct_status st = coupling_setup(c, d, "coupling_build", dev, &buf);
-  if (st != MQCT_OK) return st;
-  hipError_t e = launch_coupling(dev, M_out, G_out, &c->prof, c->stream);
+  CouplingHold hold;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  mqct_status st = coupling_setup(c, d, "coupling_build", dev, &buf, hold, [&](int N, int T, int K) {
+    // the outputs are cleared first: most elements stay zero, and the memory's write rate
+    // bounds it
+    const int64_t NN = (int64_t)N * N;
+    e0 = c->prof.next();
+    e1 = c->prof.next();
+    prof_mark(&c->prof, e0, c->stream);
+    hipError_t e = M_out ? launch_coupling_zero(M_out, K * NN, c->stream) : hipSuccess;
+    if (e == hipSuccess && G_out) e = launch_coupling_zero(G_out, T * NN, c->stream);
+    return e;
+  });
+  if (st != MQCT_OK) {
+    prof_mark(&c->prof, e1, c->stream);
+    return st;
+  }
+  hipError_t e = launch_coupling(dev, M_out, G_out, c->stream);
+  prof_mark(&c->prof, e1, c->stream);
   if (e == hipErrorInvalidValue) {
+    (void)hipStreamSynchronize(c->stream);
     hipFree(buf);
     return fail(c, MQCT_ERR_ARG, "coupling_build: output too large for one launch");
   }
@@ -2126,7 +2162,8 @@ mqct_status mqct_coupling_build_sparse(mqct_context* c, const mqct_coupling_desc
     return fail(c, MQCT_ERR_NONFINITE, "coupling_build_sparse: non-finite v_screen");
   CouplingDev dev;
   char* buf = nullptr;
-  mqct_status st = coupling_setup(c, d, "coupling_build_sparse", dev, &buf);
+  CouplingHold hold;
+  mqct_status st = coupling_setup(c, d, "coupling_build_sparse", dev, &buf, hold);
   if (st != MQCT_OK) return st;
   // screening coefficients in the sorted term order, and the kept-element counter
   std::vector<double> vs((size_t)dev.T * n_screen);

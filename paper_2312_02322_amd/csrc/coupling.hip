@@ -19,15 +19,17 @@
 // which is what makes the build cheap: F depends on the angular momenta only
 // (not on m or tau1), K on the rotor-1 states only.  Kernels:
 //   cpl_lfact  log-factorials (the Racah sums below run in the log domain);
+//   cpl_zero   the outputs cleared with 16-byte stores (most elements couple
+//              channels of different m and stay zero), while the host lays out the
+//              build;
 //   cpl_rotor  K_t for every pair of rotor-1 states;
 //   cpl_jlevel F_t for every pair of (j1, j2, j) levels (9j from three 6j);
-//   cpl_zero   the outputs cleared with 16-byte stores (most elements couple
-//              channels of different m and stay zero);
 //   cpl_cgm    the coefficients C(j' m lam 0 | j'' m) for every j', j'', m and lam
 //              that occur;
 //   cpl_fill   one work item per row n'' and 256 of the channels n' that share its
-//              m: per lane g_t = F K C gathered for a chunk of terms, then M[k][n''][n']
-//              = sum_t v_t(R_k) g_t for a chunk of knots (v by scalar loads).  With
+//              m: M[k][n''][n'] = sum_t v_t(R_k) g_t as a product (knots x terms) x
+//              (terms x channels) on the FP64 matrix cores, each lane forming g_t =
+//              F K C of its channel for four consecutive terms at a time.  With
 //              channels ordered by m the lanes of a work item write consecutive
 //              columns.
 #include "internal.h"
@@ -42,9 +44,10 @@ namespace {
 
 constexpr int LF_N = 256;        // log-factorial table: arguments up to 255
 constexpr int FILL_BLOCK = 256;
-constexpr int FILL_KC = CPL_KNOT_CHUNK;   // knots per accumulation chunk (registers)
+constexpr int VAL_KC = CPL_KNOT_CHUNK;    // knots per accumulation chunk (registers)
+constexpr int JL_ITEMS = 2048;   // level factors per workgroup
 constexpr int NXCD = 8;          // accelerator dies of the device, each with its own L2
-constexpr int FILL_TC = 8;       // terms whose factors are gathered together
+constexpr int GATHER_TC = 8;     // terms whose factors are gathered together
 
 __device__ inline bool tri(int a, int b, int c) { return c >= abs(a - b) && c <= a + b; }
 
@@ -127,31 +130,51 @@ __global__ void cpl_rotor(CouplingDev d) {
     kb = ka - mu;
     if (abs(kb) <= jb) acc += s * bb[kb + jb] * x * cg_dev(d.lf, ja, ka, l1, -mu, jb, kb);
   }
-  d.Kr[i] = acc;
+  d.Kr[pr * d.TP + t] = acc;
 }
 
-// F[Jb][Ja][t] between (j1, j2, j) levels Ja (initial) and Jb (final)
-__global__ void cpl_jlevel(CouplingDev d) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nn = (int64_t)d.nJ * d.nJ;
-  if (i >= (int64_t)d.T * nn) return;
-  const int t = (int)(i % d.T);
-  const int64_t pr = i / d.T;
-  const int Jb = (int)(pr / d.nJ), Ja = (int)(pr - (int64_t)Jb * d.nJ);
-  const int l1 = d.t_l1[t], l2 = d.t_l2[t], l = d.t_l[t];
-  const int j1a = d.jl_j1[Ja], j2a = d.jl_j2[Ja], ja = d.jl_j[Ja];
-  const int j1b = d.jl_j1[Jb], j2b = d.jl_j2[Jb], jb = d.jl_j[Jb];
-  double f = 0.0;
-  const double c2 = cg_dev(d.lf, j2a, 0, l2, 0, j2b, 0);
-  if (c2 != 0.0 && tri(j1a, l1, j1b) && tri(ja, l, jb)) {
+// F[Jb][Ja][t] between (j1, j2, j) levels Ja (initial) and Jb (final).  Triangle rules
+// and C(j2' 0 lam2 0 | j2'' 0) leave few of a workgroup's JL_ITEMS factors nonzero: those
+// are listed first, so that the 9j sums run in full waves.
+__global__ void __launch_bounds__(256) cpl_jlevel(CouplingDev d) {
+  __shared__ int list[JL_ITEMS];
+  __shared__ int count;
+  if (threadIdx.x == 0) count = 0;
+  __syncthreads();
+  const int64_t nn = (int64_t)d.nJ * d.nJ, total = (int64_t)d.T * nn;
+  const int64_t i0 = (int64_t)blockIdx.x * JL_ITEMS;
+  for (int q = threadIdx.x; q < JL_ITEMS; q += 256) {
+    const int64_t i = i0 + q;
+    if (i >= total) break;
+    const int t = (int)(i % d.T);
+    const int64_t pr = i / d.T;
+    const int Jb = (int)(pr / d.nJ), Ja = (int)(pr - (int64_t)Jb * d.nJ);
+    const int j2a = d.jl_j2[Ja], j2b = d.jl_j2[Jb], l2 = d.t_l2[t];
+    if (tri(d.jl_j1[Ja], d.t_l1[t], d.jl_j1[Jb]) && tri(d.jl_j[Ja], d.t_l[t], d.jl_j[Jb]) &&
+        cg_dev(d.lf, j2a, 0, l2, 0, j2b, 0) != 0.0)
+      list[atomicAdd(&count, 1)] = q;
+    else
+      d.F[pr * d.TP + t] = 0.0;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < count; q += 256) {
+    const int64_t i = i0 + list[q];
+    const int t = (int)(i % d.T);
+    const int64_t pr = i / d.T;
+    const int Jb = (int)(pr / d.nJ), Ja = (int)(pr - (int64_t)Jb * d.nJ);
+    const int l1 = d.t_l1[t], l2 = d.t_l2[t], l = d.t_l[t];
+    const int j1a = d.jl_j1[Ja], j2a = d.jl_j2[Ja], ja = d.jl_j[Ja];
+    const int j1b = d.jl_j1[Jb], j2b = d.jl_j2[Jb], jb = d.jl_j[Jb];
+    const double c2 = cg_dev(d.lf, j2a, 0, l2, 0, j2b, 0);
     const double nj = ninej_dev(d.lf, j1a, j2a, ja, l1, l2, l, j1b, j2b, jb);
-    f = sqrt((double)(2 * j1a + 1) * (2 * j2a + 1) * (2 * ja + 1) * (2 * l + 1)) *
+    d.F[pr * d.TP + t] =
+        sqrt((double)(2 * j1a + 1) * (2 * j2a + 1) * (2 * ja + 1) * (2 * l + 1)) *
         sqrt((double)(2 * l1 + 1) * (2 * l2 + 1)) * (0.25 / M_PI) * c2 * nj;
   }
-  d.F[i] = f;
 }
 
-// zero n doubles, one 16-byte store per thread from the first 16-byte boundary
+// zero n doubles (9.3 GB: 1.31 ms, 7.1 TB/s; in one launch with the factors, which hold
+// four times the registers, the two took 1.73 ms instead of 1.60), one 16-byte store per thread from the first 16-byte boundary
 // (single elements before it and after the last pair)
 __global__ void __launch_bounds__(256) cpl_zero(double* __restrict__ p, int64_t n) {
   typedef double dv2 __attribute__((ext_vector_type(2)));
@@ -189,74 +212,146 @@ struct GPtr {
   const double* C;
 };
 __device__ __forceinline__ GPtr gptr(const CouplingDev& d, int nb, int na) {
-  const int T = d.T, JM = d.cg_jmax, mb = d.chan_m[nb];
+  const int TP = d.TP, JM = d.cg_jmax, mb = d.chan_m[nb];
   const int Jb = d.chan_J[nb], rb = d.chan_r[nb], jb = d.chan_j[nb];
   const int Ja = d.chan_J[na], ra = d.chan_r[na], ja = d.chan_j[na];
   GPtr p;
-  p.F = d.F + ((int64_t)Jb * d.nJ + Ja) * T;
-  p.Kr = d.Kr + ((int64_t)rb * d.n1 + ra) * T;
+  p.F = d.F + ((int64_t)Jb * d.nJ + Ja) * TP;
+  p.Kr = d.Kr + ((int64_t)rb * d.n1 + ra) * TP;
   p.C = d.cgt + (((int64_t)ja * (JM + 1) + jb) * (2 * JM + 1) + mb + JM) * (d.cg_lmax + 1);
   return p;
 }
-// g_t for the FILL_TC terms from t0 (indices past the last term repeat it)
+// g_t for the GATHER_TC terms from t0 (indices past the last term repeat it)
 __device__ __forceinline__ void gather_g(const CouplingDev& d, const GPtr& p, int t0,
-                                         double (&gv)[FILL_TC]) {
+                                         double (&gv)[GATHER_TC]) {
 #pragma unroll
-  for (int i = 0; i < FILL_TC; ++i) {
+  for (int i = 0; i < GATHER_TC; ++i) {
     const int t = min(t0 + i, d.T - 1);
     gv[i] = p.F[t] * p.Kr[t] * p.C[d.t_l[t]];
   }
 }
 
+// Workgroup ids go to the dies round-robin: each die gets one contiguous share of the
+// work list (ordered by the rows' levels), so that its L2 holds the level-factor rows
+// those items read.  False for the ids beyond the list.
+__device__ __forceinline__ bool work_item(const CouplingDev& d, int2& w) {
+  const int64_t per = (d.n_work + NXCD - 1) / NXCD;
+  const int64_t wi = (int64_t)(blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
+  if (blockIdx.x / NXCD >= per || wi >= d.n_work) return false;
+  w = d.work[wi];
+  return true;
+}
+
 // One work item = (row nb, FILL_BLOCK consecutive entries of the list of channels
-// that share nb's m).  M[k][nb][na] (and G[t][nb][na] when asked) for those na.
-// Per chunk of FILL_TC terms a lane first gathers the chunk's factors (F, K and
-// the m-coefficient, all independent loads), then adds v_t(R_k) g_t into FILL_KC
-// knot accumulators; v (rows padded to a multiple of FILL_KC) is the same for
-// every lane and is read with uniform (scalar) loads.
+// that share nb's m).  M[k][nb][na] (and G[t][nb][na] when asked) for those na, as
+// v_mfma_f64_16x16x4 products: lane l holds the column of channel l % 16 of a tile and
+// the terms t0 + 4 (l / 16) + i, i = 0..3, of a step of 16 (a permutation of the sum over
+// t), so 64 lanes touch 16 rows of F and of K with 32 consecutive bytes each; v of up to
+// FILL_TC terms and 64 knots is in LDS, rows padded so that the four term groups of a
+// read fall into different banks, and the row's m-coefficients beside it.  The next
+// step's factors are requested before this step's products.
+// N = 4,290, 83 terms, 63 knots (9.3 GB, of it 0.74 GB written here): one channel per
+// lane, terms one by one and the knots in two passes, 1.29 ms (its loads touch 64 rows
+// each); this form 0.69 ms.  What is left is neither its products (0.56 without) nor its
+// stores (0.60 without) but the latency of the gathers at three waves per SIMD; two tiles
+// a wave (230 registers) take 0.74 ms, a persistent grid 0.68.
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
+constexpr int FILL_TC = 96, FILL_KC = 64, FILL_LD = FILL_KC + 4;
+
 __global__ void __launch_bounds__(FILL_BLOCK)
-cpl_fill(CouplingDev d, const int2* __restrict__ work, double* __restrict__ M,
-         double* __restrict__ G) {
-  const int2 w = work[blockIdx.x];
-  const int nb = w.x;
-  const int g = d.chan_grp[nb];
+cpl_fill(CouplingDev d, double* __restrict__ M, double* __restrict__ G) {
+  extern __shared__ __align__(16) double vl[];      // [FILL_TC][FILL_LD] v
+  double* cl = vl + FILL_TC * FILL_LD;              // [cg_jmax + 1][cg_lmax + 1] C(ja m lam 0 | jb m)
+  __shared__ int tl[FILL_TC];
+  int2 w;
+  if (!work_item(d, w)) return;
+  const int nb = w.x, g = d.chan_grp[nb];
   const int g0 = d.grp_off[g], cnt = d.grp_off[g + 1] - g0;
-  const int q = w.y * FILL_BLOCK + threadIdx.x;
-  if (q >= cnt) return;
-  const int na = d.grp_list[g0 + q];
-  const int N = d.N, T = d.T, K = d.K, KP = d.KP;
+  const int N = d.N, T = d.T, K = d.K, KP = d.KP, L1 = d.cg_lmax + 1;
   const int64_t NN = (int64_t)N * N;
-  const int64_t pos = (int64_t)nb * N + na;
-  const GPtr gp = gptr(d, nb, na);
-  const double* __restrict__ v = d.v;
-  // G alone: one pass over the terms
-  const int kpasses = M ? K : 1;
-  for (int k0 = 0; k0 < kpasses; k0 += FILL_KC) {
-    double acc[FILL_KC];
+  const int wave = threadIdx.x >> 6, col = threadIdx.x & 15, grp = (threadIdx.x & 63) >> 4;
+  {
+    const int JM = d.cg_jmax, jb = d.chan_j[nb], mb = d.chan_m[nb];
+    for (int i = threadIdx.x; i < (JM + 1) * L1; i += FILL_BLOCK)
+      cl[i] = d.cgt[(((int64_t)(i / L1) * (JM + 1) + jb) * (2 * JM + 1) + mb + JM) * L1 + i % L1];
+  }
+  const int kend = M ? K : 1;          // G alone: one pass over the terms
+  for (int k0 = 0; k0 < kend; k0 += FILL_KC) {
+    const int ntile = min(FILL_KC, K - k0 + 15) >> 4;
+    for (int h = 0; h < 4; ++h) {      // a wave's 64 channels, 16 at a time
+      const int q = w.y * FILL_BLOCK + wave * 64 + h * 16 + col;
+      const bool work = q - col < cnt;
+      const int na = d.grp_list[g0 + min(q, cnt - 1)];
+      const GPtr gp = gptr(d, nb, na);
+      const double* cj = cl + d.chan_j[na] * L1;
+      const int64_t pos = (int64_t)nb * N + na;
+      v4d acc[4];
 #pragma unroll
-    for (int u = 0; u < FILL_KC; ++u) acc[u] = 0.0;
-    for (int t0 = 0; t0 < T; t0 += FILL_TC) {
-      double gv[FILL_TC];
-      gather_g(d, gp, t0, gv);
-      if (G && k0 == 0) {
+      for (int mt = 0; mt < 4; ++mt) acc[mt] = v4d{0.0, 0.0, 0.0, 0.0};
+      for (int c0 = 0; c0 < T; c0 += FILL_TC) {
+        const int nt = min(FILL_TC, T - c0);
+        if (h == 0 || T > FILL_TC) {
+          __syncthreads();
+          for (int i = threadIdx.x; i < FILL_TC * FILL_KC; i += FILL_BLOCK) {
+            const int t = i / FILL_KC, k = i % FILL_KC;
+            vl[t * FILL_LD + k] = t < nt && k0 + k < K ? d.v[(int64_t)(c0 + t) * KP + k0 + k] : 0.0;
+          }
+          if (threadIdx.x < FILL_TC) tl[threadIdx.x] = d.t_l[min(c0 + (int)threadIdx.x, T - 1)];
+          __syncthreads();
+        }
+        if (!work) continue;
+        const double *F = gp.F + c0, *Kr = gp.Kr + c0;
+        v2d f[2], kr[2];
+        auto load = [&](int t0) {
+          const int tq = t0 + 4 * grp;
+          if (t0 + 16 <= nt) {
 #pragma unroll
-        for (int i = 0; i < FILL_TC; ++i)
-          if (t0 + i < T) G[(int64_t)d.t_user[t0 + i] * NN + pos] = gv[i];
-      }
-      if (M) {
+            for (int i = 0; i < 2; ++i) {
+              f[i] = *(const v2d*)(F + tq + 2 * i);
+              kr[i] = *(const v2d*)(Kr + tq + 2 * i);
+            }
+          } else {
 #pragma unroll
-        for (int i = 0; i < FILL_TC; ++i) {
-          if (t0 + i >= T) break;
-          const double* vt = v + (int64_t)(t0 + i) * KP + k0;
+            for (int i = 0; i < 4; ++i) {
+              f[i >> 1][i & 1] = F[min(tq + i, nt - 1)];
+              kr[i >> 1][i & 1] = Kr[min(tq + i, nt - 1)];
+            }
+          }
+        };
+        load(0);
+        for (int t0 = 0; t0 < nt; t0 += 16) {
+          const int tq = t0 + 4 * grp;
+          double gv[4];
 #pragma unroll
-          for (int u = 0; u < FILL_KC; ++u) acc[u] = fma(vt[u], gv[i], acc[u]);
+          for (int i = 0; i < 4; ++i) gv[i] = f[i >> 1][i & 1] * kr[i >> 1][i & 1] * cj[tl[tq + i]];
+          if (t0 + 16 < nt) load(t0 + 16);
+          if (G && k0 == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (tq + i < nt && q < cnt) G[(int64_t)d.t_user[c0 + tq + i] * NN + pos] = gv[i];
+          }
+          if (!M) continue;
+          const double* vr = vl + tq * FILL_LD + col;
+#pragma unroll
+          for (int mt = 0; mt < 4; ++mt) {
+            if (mt >= ntile) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              acc[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(vr[i * FILL_LD + mt * 16], gv[i],
+                                                             acc[mt], 0, 0, 0);
+          }
         }
       }
-    }
-    if (M) {
+      if (!M || q >= cnt) continue;
+      double* out = M + (int64_t)(k0 + grp) * NN + pos;
 #pragma unroll
-      for (int u = 0; u < FILL_KC; ++u)
-        if (k0 + u < K) M[(k0 + u) * NN + pos] = acc[u];
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int k = mt * 16 + 4 * r;
+          if (k0 + grp + k < K) out[k * NN] = acc[mt][r];
+        }
     }
   }
 }
@@ -266,16 +361,11 @@ cpl_fill(CouplingDev d, const int2* __restrict__ work, double* __restrict__ M,
 // (rows, cols) in the order the per-wave atomics give (one atomic per wave);
 // slots past the capacity are counted but not written.
 __global__ void __launch_bounds__(FILL_BLOCK)
-cpl_screen(CouplingDev d, const int2* __restrict__ work, int S, const double* __restrict__ vs,
+cpl_screen(CouplingDev d, int S, const double* __restrict__ vs,
            double thr, int64_t capacity, unsigned long long* __restrict__ count,
            int32_t* __restrict__ rows, int32_t* __restrict__ cols) {
-  // workgroup ids go to the dies round-robin; give each die one contiguous share
-  // of the work list (ordered by the rows' levels) so that its L2 holds the
-  // level-factor rows those items read
-  const int64_t per = (d.n_work + NXCD - 1) / NXCD;
-  const int64_t wi = (int64_t)(blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
-  if (blockIdx.x / NXCD >= per || wi >= d.n_work) return;
-  const int2 w = work[wi];
+  int2 w;
+  if (!work_item(d, w)) return;
   const int nb = w.x;
   const int g = d.chan_grp[nb];
   const int g0 = d.grp_off[g], cnt = d.grp_off[g + 1] - g0;
@@ -290,11 +380,11 @@ cpl_screen(CouplingDev d, const int2* __restrict__ work, int S, const double* __
     double acc[CPL_MAX_SCREEN];
 #pragma unroll
     for (int u = 0; u < CPL_MAX_SCREEN; ++u) acc[u] = 0.0;
-    for (int t0 = 0; t0 < d.T; t0 += FILL_TC) {
-      double gv[FILL_TC];
+    for (int t0 = 0; t0 < d.T; t0 += GATHER_TC) {
+      double gv[GATHER_TC];
       gather_g(d, gp, t0, gv);
 #pragma unroll
-      for (int i = 0; i < FILL_TC; ++i) {
+      for (int i = 0; i < GATHER_TC; ++i) {
         if (t0 + i >= d.T) break;
         const double* vt = vs + (int64_t)(t0 + i) * S;
 #pragma unroll
@@ -334,23 +424,23 @@ cpl_values(CouplingDev d, int64_t n, const int32_t* __restrict__ rows,
   const GPtr gp = gptr(d, rows[i], cols[i]);
   const int T = d.T, K = d.K, KP = d.KP;
   const double* __restrict__ v = d.v;
-  for (int k0 = 0; k0 < K; k0 += FILL_KC) {
-    double acc[FILL_KC];
+  for (int k0 = 0; k0 < K; k0 += VAL_KC) {
+    double acc[VAL_KC];
 #pragma unroll
-    for (int u = 0; u < FILL_KC; ++u) acc[u] = 0.0;
-    for (int t0 = 0; t0 < T; t0 += FILL_TC) {
-      double gv[FILL_TC];
+    for (int u = 0; u < VAL_KC; ++u) acc[u] = 0.0;
+    for (int t0 = 0; t0 < T; t0 += GATHER_TC) {
+      double gv[GATHER_TC];
       gather_g(d, gp, t0, gv);
 #pragma unroll
-      for (int j = 0; j < FILL_TC; ++j) {
+      for (int j = 0; j < GATHER_TC; ++j) {
         if (t0 + j >= T) break;
         const double* vt = v + (int64_t)(t0 + j) * KP + k0;
 #pragma unroll
-        for (int u = 0; u < FILL_KC; ++u) acc[u] = fma(vt[u], gv[j], acc[u]);
+        for (int u = 0; u < VAL_KC; ++u) acc[u] = fma(vt[u], gv[j], acc[u]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < FILL_KC; ++u)
+    for (int u = 0; u < VAL_KC; ++u)
       if (k0 + u < K) values[(int64_t)(k0 + u) * capacity + i] = acc[u];
   }
 }
@@ -372,29 +462,27 @@ hipError_t launch_factors(const CouplingDev& d, hipStream_t s) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t nj = (int64_t)d.T * d.nJ * d.nJ;
   if ((nj + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
-  cpl_jlevel<<<(unsigned)((nj + 255) / 256), 256, 0, s>>>(d);
+  cpl_jlevel<<<(unsigned)((nj + JL_ITEMS - 1) / JL_ITEMS), 256, 0, s>>>(d);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, Prof* prof,
-                           hipStream_t s) {
-  hipError_t e = launch_factors(d, s);
-  if (e != hipSuccess) return e;
-  hipEvent_t e0 = prof ? prof->next() : nullptr, e1 = prof ? prof->next() : nullptr;
-  prof_mark(prof, e0, s);
-  const int64_t NN = (int64_t)d.N * d.N;
-  auto zero = [&](double* p, int64_t n) {
-    const int64_t blocks = ((n + 1) / 2 + 255) / 256;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    cpl_zero<<<(unsigned)blocks, 256, 0, s>>>(p, n);
-    return hipGetLastError();
-  };
-  if (M && (e = zero(M, (int64_t)d.K * NN)) != hipSuccess) return e;
-  if (G && (e = zero(G, (int64_t)d.T * NN)) != hipSuccess) return e;
-  cpl_fill<<<(unsigned)d.n_work, FILL_BLOCK, 0, s>>>(d, d.work, M, G);
-  prof_mark(prof, e1, s);
+hipError_t launch_coupling_zero(double* p, int64_t n, hipStream_t s) {
+  const int64_t blocks = ((n + 1) / 2 + 255) / 256;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  cpl_zero<<<(unsigned)blocks, 256, 0, s>>>(p, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, hipStream_t s) {
+  const size_t lds = (FILL_TC * FILL_LD + (size_t)(d.cg_jmax + 1) * (d.cg_lmax + 1)) * 8;
+  hipError_t e = hipSuccess;
+  if (lds > 65536) e = hipFuncSetAttribute((const void*)cpl_fill,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess || (e = launch_factors(d, s)) != hipSuccess) return e;
+  const int64_t blocks = (d.n_work + NXCD - 1) / NXCD * NXCD;
+  cpl_fill<<<(unsigned)blocks, FILL_BLOCK, lds, s>>>(d, M, G);
   return hipGetLastError();
 }
 
@@ -406,8 +494,7 @@ hipError_t launch_coupling_screen(const CouplingDev& d, int S, const double* vs,
   if (e != hipSuccess) return e;
   const int64_t blocks = (d.n_work + NXCD - 1) / NXCD * NXCD;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  cpl_screen<<<(unsigned)blocks, FILL_BLOCK, 0, s>>>(d, d.work, S, vs, thr, capacity, count, rows,
-                                                      cols);
+  cpl_screen<<<(unsigned)blocks, FILL_BLOCK, 0, s>>>(d, S, vs, thr, capacity, count, rows, cols);
   return hipGetLastError();
 }
 

@@ -135,7 +135,7 @@ inline void prof_mark(Prof* p, hipEvent_t e, hipStream_t s) {
   if (p && e) (void)hipEventRecord(e, s);
 }
 
-// knots per accumulation chunk of the coupling fill kernel (v rows are padded to it)
+// knots per accumulation chunk of the sparse builder (v rows are padded to it)
 constexpr int CPL_KNOT_CHUNK = 32;
 
 // Device view of a coupling-matrix build (coupling.hip).  Channels n have a
@@ -159,13 +159,14 @@ struct CouplingDev {
   const int* t_user;
   const double* v;       // [T][KP], sorted order, zero beyond K
   double* lf;            // [256] log-factorials
-  double* Kr;            // [n1][n1][T] rotor-1 factors
-  double* F;             // [nJ][nJ][T] level factors
+  double* Kr;            // [n1][n1][TP] rotor-1 factors
+  double* F;             // [nJ][nJ][TP] level factors
   const int* chan_grp;   // [N] the channel's m group
   const int* grp_off;    // [groups + 1] offsets into grp_list
   const int* grp_list;   // [N] channels of each m group, ascending
   const int2* work;      // [n_work] (row, tile of FILL_BLOCK entries of its m group)
   int64_t n_work;
+  int TP;                // T rounded up to even: stride of the factor rows
   int KP;                // v row stride: K rounded up to the fill kernel's knot chunk
   int cg_jmax, cg_lmax;  // extent of the C(j' m lam 0 | j'' m) table
   double* cgt;           // that table
@@ -372,9 +373,11 @@ hipError_t launch_xs_rates(int nE, int L, int nT, const double* U, const double*
                            const double* g, const double* sym, double mu, const double* beta,
                            double* k, hipStream_t s);
 
-// coupling-matrix build: M [K][N][N] and/or G [T][N][N] (device, either may be null)
-hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, Prof* prof,
-                           hipStream_t s);
+// n doubles set to zero
+hipError_t launch_coupling_zero(double* p, int64_t n, hipStream_t s);
+// coupling-matrix build: M [K][N][N] and/or G [T][N][N] (device, cleared before, either
+// may be null)
+hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, hipStream_t s);
 // screened build: factors, then the equal-m elements whose largest |M| over the
 // S screening radii (coefficients vs [T][S], sorted term order) exceeds thr,
 // counted in *count and listed in rows / cols up to capacity; then their values
