@@ -37,10 +37,10 @@ MEASURED_TRAFFIC = {
     # FETCH_SIZE (x 1.99992, the copy calibration) + WRITE_SIZE of bin_gemm<C64> per
     # launch, taken on this source revision: the N=969 window (mean of the 41 launches
     # of one bench step) and the N=4096 collision (mean of all 40,020 launches)
-    ("C64", "binned"): {"source": "binned.hip", "source_sha256_16": "36178d36d14d6324",
+    ("C64", "binned"): {"source": "binned.hip", "source_sha256_16": "b326280595df78f6",
                         "bytes": 2.928e9, "window": 10, "trajectories": 4096},
-    ("C64", "large"): {"source": "binned.hip", "source_sha256_16": "36178d36d14d6324",
-                       "bytes": 1.9866e10, "trajectories": 512},
+    ("C64", "large"): {"source": "binned.hip", "source_sha256_16": "b326280595df78f6",
+                       "bytes": 2.0103e10, "trajectories": 512},
 }
 
 
