@@ -555,7 +555,9 @@ mqct_status mqct_rate_coefficients(mqct_context* ctx, int32_t mem, int32_t n_E, 
  *   lam2, lam          |lam1 - lam2| <= lam <= lam1 + lam2;
  *   K, v               radial coefficients v[t * K + k] (hartree) at the knots.
  * j2 <= 40.  Errors: MQCT_ERR_ARG (bad sizes, indices, angular momenta, null
- * pointers), MQCT_ERR_NONFINITE (b or v), MQCT_ERR_OOM / MQCT_ERR_DEVICE.
+ * pointers), MQCT_ERR_NONFINITE (b or v), MQCT_ERR_OOM / MQCT_ERR_DEVICE.  Except
+ * for MQCT_ERR_DEVICE they leave the outputs untouched; every return leaves
+ * nothing of the call in flight.
  * The Clebsch-Gordan, 6j and 9j coefficients are formed in FP64 from
  * log-factorials; their relative error grows with the angular momenta (measured
  * against long-double sums: 2e-14 of the largest element for j <= 13, 3e-13 for
@@ -618,8 +620,9 @@ mqct_status mqct_coupling_build_sparse(mqct_context* ctx, const mqct_coupling_de
  *                 the final diagnostic one); binned product, the value and
  *                 second-derivative slices of every occupied knot once per stage
  *                 (counted on the device); 0 for the work-list schedule;
- *                 for mqct_coupling_build (whose fill kernel is timed), the
- *                 bytes it wrote (M_out and G_out).
+ *                 for mqct_coupling_build (whose clearing and fill kernels
+ *                 are timed, one launch a call), the bytes it wrote (M_out and
+ *                 G_out).
  * and resets them.  Timing adds two event records per timed launch.
  */
 mqct_status mqct_set_profiling(mqct_context* ctx, int32_t enable);

@@ -1954,16 +1954,17 @@ namespace {
 // (j1, j2, j) levels, terms sorted by lam, channels grouped by m, the work list
 // (per row, tiles of 256 channels of the row's m group), and one device
 // workspace holding them with the factor arrays.  On success *buf owns it.  With early,
-// that is called once the arguments are known to be good: what it enqueues runs while the
-// host lays out the rest, whose uploads are then ordered on the stream and read `hold`
-// until the stream has been waited for.
+// that is called once nothing but the device itself can fail any more (arguments good,
+// launch limits held, workspace allocated): what it enqueues runs while the host lays out
+// the rest, whose uploads are then ordered on the stream and read `hold` until the stream
+// has been waited for.  On failure nothing is in flight.
 struct CouplingHold {
   std::vector<int32_t> ints;
   std::vector<double> vs;
 };
 mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const char* what,
-                           CouplingDev& dev, char** buf, CouplingHold& hold,
-                           const std::function<hipError_t(int, int, int)>& early = nullptr) {
+                           CouplingDev& dev, char** buf, CouplingHold& hold, bool M, bool G,
+                           const std::function<hipError_t()>& early = nullptr) {
   *buf = nullptr;
   if (!d) return fail(c, MQCT_ERR_ARG, "%s: null descriptor", what);
   const int N = d->N, T = d->T, K = d->K, n1 = d->n_rot1, bs = d->b_stride;
@@ -1972,15 +1973,17 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
   if (!d->j || !d->m || !d->rot1 || !d->j2 || !d->rot1_j || !d->b || !d->lam1 || !d->mu1 ||
       !d->lam2 || !d->lam || !d->v)
     return fail(c, MQCT_ERR_ARG, "%s: null array", what);
-  constexpr int JMAX = 40, LMAX = 20;
+  constexpr int JMAX = 40, LMAX = 20, MMAX = 2 * JMAX;
   for (int r = 0; r < n1; ++r)
     if (d->rot1_j[r] < 0 || d->rot1_j[r] > JMAX || 2 * d->rot1_j[r] + 1 > bs)
       return fail(c, MQCT_ERR_ARG, "%s: rotor-1 state %d: j1 out of 0..%d or b_stride too small",
                   what, r, JMAX);
   if (!finite_arr(d->b, (int64_t)n1 * bs) || !finite_arr(d->v, (int64_t)T * K))
     return fail(c, MQCT_ERR_NONFINITE, "%s: non-finite b or v", what);
-  std::map<std::pair<int, std::pair<int, int>>, int> jl;
+  std::vector<int32_t> level((size_t)(JMAX + 1) * (JMAX + 1) * (MMAX + 1), -1);
   std::vector<int32_t> jl_j1, jl_j2, jl_j, chan_J(N);
+  int64_t of_m[2 * MMAX + 1] = {};   // channels of each m
+  int cg_lmax = 0, cg_jmax = 0;
   for (int n = 0; n < N; ++n) {
     const int r = d->rot1[n], j2 = d->j2[n], j = d->j[n], m = d->m[n];
     if (r < 0 || r >= n1) return fail(c, MQCT_ERR_ARG, "%s: rot1[%d] out of range", what, n);
@@ -1988,15 +1991,16 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
     if (j2 < 0 || j2 > JMAX || j < std::abs(j1 - j2) || j > j1 + j2 || std::abs(m) > j)
       return fail(c, MQCT_ERR_ARG, "%s: channel %d: need 0 <= j2 <= %d, |j1-j2| <= j <= j1+j2, "
                   "|m| <= j", what, n, JMAX);
-    auto key = std::make_pair(j1, std::make_pair(j2, j));
-    auto it = jl.find(key);
-    if (it == jl.end()) {
-      it = jl.emplace(key, (int)jl_j1.size()).first;
+    int32_t& lv = level[((size_t)j1 * (JMAX + 1) + j2) * (MMAX + 1) + j];
+    if (lv < 0) {
+      lv = (int32_t)jl_j1.size();
       jl_j1.push_back(j1);
       jl_j2.push_back(j2);
       jl_j.push_back(j);
     }
-    chan_J[n] = it->second;
+    chan_J[n] = lv;
+    ++of_m[m + MMAX];
+    cg_jmax = std::max(cg_jmax, j);
   }
   const int nJ = (int)jl_j1.size();
   std::vector<int32_t> perm(T);
@@ -2007,85 +2011,96 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
       return fail(c, MQCT_ERR_ARG, "%s: term %d: need 0 <= lam1, lam2 <= %d, |mu1| <= lam1, "
                   "|lam1-lam2| <= lam <= lam1+lam2", what, t, LMAX);
     perm[t] = t;
+    cg_lmax = std::max(cg_lmax, l);
   }
-  HIP_TRY(c, hipSetDevice(c->device), what);
-  hipError_t e = early ? early(N, T, K) : hipSuccess;
-  if (e == hipErrorInvalidValue)
-    return fail(c, MQCT_ERR_ARG, "%s: output too large for one launch", what);
-  if (e != hipSuccess) return hip_fail(c, e, what);
-  // terms sorted by lam (kept from the first form of the fill kernel; the order of
-  // the sums over t is then the same in every kernel)
-  std::stable_sort(perm.begin(), perm.end(),
-                   [&](int a, int b) { return d->lam[a] < d->lam[b]; });
-  std::vector<int32_t>& ints = hold.ints;
-  auto put = [&](const int32_t* p, size_t n) {
-    const size_t o = ints.size();
-    ints.insert(ints.end(), p, p + n);
-    return o;
-  };
-  std::vector<int32_t> tl1(T), tmu(T), tl2(T), tl(T);
-  const int KP = (K + CPL_KNOT_CHUNK - 1) / CPL_KNOT_CHUNK * CPL_KNOT_CHUNK;
-  std::vector<double>& vs = hold.vs;
-  vs.assign((size_t)T * KP, 0.0);
-  int cg_lmax = 0, cg_jmax = 0;
-  for (int t = 0; t < T; ++t) {
-    const int u = perm[t];
-    tl1[t] = d->lam1[u]; tmu[t] = d->mu1[u]; tl2[t] = d->lam2[u]; tl[t] = d->lam[u];
-    memcpy(&vs[(size_t)t * KP], d->v + (size_t)u * K, (size_t)K * 8);
-    cg_lmax = std::max(cg_lmax, tl[t]);
-  }
-  for (int n = 0; n < N; ++n) cg_jmax = std::max(cg_jmax, (int)d->j[n]);
-  std::vector<int32_t> chan_r(d->rot1, d->rot1 + N), chan_j(d->j, d->j + N), chan_m(d->m, d->m + N);
-  std::map<int, int> gid;
-  for (int n = 0; n < N; ++n) gid.emplace(d->m[n], 0);
+  // sizes first: the m groups, the work list, the integer arrays and the workspace
   int ng = 0;
-  for (auto& kv : gid) kv.second = ng++;
-  std::vector<int32_t> chan_grp(N), grp_off(ng + 1, 0), grp_list(N);
-  for (int n = 0; n < N; ++n) {
-    chan_grp[n] = gid[d->m[n]];
-    ++grp_off[chan_grp[n] + 1];
-  }
-  for (int g = 0; g < ng; ++g) grp_off[g + 1] += grp_off[g];
-  {
-    std::vector<int32_t> fillp(grp_off.begin(), grp_off.end() - 1);
-    for (int n = 0; n < N; ++n) grp_list[fillp[chan_grp[n]]++] = n;
-  }
-  // rows taken level by level ((j1, j2, j) of the row, then m): consecutive work
-  // items then read the same row of level factors
-  std::vector<int32_t> order(N);
-  for (int n = 0; n < N; ++n) order[n] = n;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-    return chan_J[a] != chan_J[b] ? chan_J[a] < chan_J[b] : d->m[a] < d->m[b];
-  });
-  std::vector<int32_t> work;
-  for (int n : order) {
-    const int cnt = grp_off[chan_grp[n] + 1] - grp_off[chan_grp[n]];
-    for (int tile = 0; tile * 256 < cnt; ++tile) {
-      work.push_back(n);
-      work.push_back(tile);
+  int64_t n_work = 0;
+  std::vector<int32_t> grp_of(2 * MMAX + 1, 0);
+  for (int q = 0; q <= 2 * MMAX; ++q)
+    if (of_m[q] > 0) {
+      grp_of[q] = ng++;
+      n_work += of_m[q] * ((of_m[q] + 255) / 256);
     }
-  }
-  const int64_t n_work = (int64_t)work.size() / 2;
   if (n_work > 0x7fffffffLL)
     return fail(c, MQCT_ERR_ARG, "%s: too many channels for one launch", what);
-  const size_t o_cJ = put(chan_J.data(), N), o_cr = put(chan_r.data(), N),
-               o_cj = put(chan_j.data(), N), o_cm = put(chan_m.data(), N),
-               o_j1 = put(jl_j1.data(), nJ), o_j2 = put(jl_j2.data(), nJ),
-               o_jj = put(jl_j.data(), nJ), o_rj = put(d->rot1_j, n1),
-               o_t1 = put(tl1.data(), T), o_tm = put(tmu.data(), T), o_t2 = put(tl2.data(), T),
-               o_tl = put(tl.data(), T), o_tu = put(perm.data(), T),
-               o_cg = put(chan_grp.data(), N), o_go = put(grp_off.data(), ng + 1),
-               o_gl = put(grp_list.data(), N);
-  if (ints.size() & 1) ints.push_back(0);      // the work list is read as int2
-  const size_t o_wk = put(work.data(), work.size());
-  const size_t ibytes = (ints.size() * 4 + 255) / 256 * 256;
+  if (!coupling_launchable(N, T, K, n1, nJ, M, G))
+    return fail(c, MQCT_ERR_ARG, "%s: output too large for one launch", what);
+  size_t n_ints = 0;
+  auto place = [&](size_t n) {
+    const size_t o = n_ints;
+    n_ints += n;
+    return o;
+  };
+  const size_t o_cJ = place(N), o_cr = place(N), o_cj = place(N), o_cm = place(N),
+               o_j1 = place(nJ), o_j2 = place(nJ), o_jj = place(nJ), o_rj = place(n1),
+               o_t1 = place(T), o_tm = place(T), o_t2 = place(T), o_tl = place(T),
+               o_tu = place(T), o_cg = place(N), o_go = place(ng + 1), o_gl = place(N);
+  n_ints += n_ints & 1;      // the work list is read as int2
+  const size_t o_wk = place((size_t)2 * n_work);
+  const int KP = (K + CPL_KNOT_CHUNK - 1) / CPL_KNOT_CHUNK * CPL_KNOT_CHUNK;
+  const size_t ibytes = (n_ints * 4 + 255) / 256 * 256;
   const int TP = (T + 1) & ~1;
   const size_t n_b = ((size_t)n1 * bs + 1) & ~(size_t)1, n_v = (size_t)T * KP, n_lf = 256;
   const size_t n_K = (size_t)TP * n1 * n1, n_F = (size_t)TP * nJ * nJ;
   const size_t n_cg = (size_t)(cg_jmax + 1) * (cg_jmax + 1) * (2 * cg_jmax + 1) * (cg_lmax + 1);
   const size_t total = ibytes + (n_b + n_v + n_lf + n_K + n_F + n_cg) * 8;
+  hold.ints.assign(n_ints, 0);
+  hold.vs.assign(n_v, 0.0);
+  std::vector<int32_t> order(N), fillp(ng);
+  HIP_TRY(c, hipSetDevice(c->device), what);
   char* w = nullptr;
-  if ((e = dev_malloc((void**)&w, total)) != hipSuccess) return hip_fail(c, e, what);
+  hipError_t e = dev_malloc((void**)&w, total);
+  if (e != hipSuccess) return hip_fail(c, e, what);
+  auto drop = [&](hipError_t err) {
+    if (early) (void)hipStreamSynchronize(c->stream);
+    hipFree(w);
+    return hip_fail(c, err, what);
+  };
+  if (early && (e = early()) != hipSuccess) return drop(e);
+  // terms sorted by lam (kept from the first form of the fill kernel; the order of
+  // the sums over t is then the same in every kernel)
+  std::stable_sort(perm.begin(), perm.end(),
+                   [&](int a, int b) { return d->lam[a] < d->lam[b]; });
+  int32_t* in = hold.ints.data();
+  for (int t = 0; t < T; ++t) {
+    const int u = perm[t];
+    in[o_t1 + t] = d->lam1[u];
+    in[o_tm + t] = d->mu1[u];
+    in[o_t2 + t] = d->lam2[u];
+    in[o_tl + t] = d->lam[u];
+    in[o_tu + t] = u;
+    memcpy(&hold.vs[(size_t)t * KP], d->v + (size_t)u * K, (size_t)K * 8);
+  }
+  std::copy(chan_J.begin(), chan_J.end(), in + o_cJ);
+  std::copy(d->rot1, d->rot1 + N, in + o_cr);
+  std::copy(d->j, d->j + N, in + o_cj);
+  std::copy(d->m, d->m + N, in + o_cm);
+  std::copy(jl_j1.begin(), jl_j1.end(), in + o_j1);
+  std::copy(jl_j2.begin(), jl_j2.end(), in + o_j2);
+  std::copy(jl_j.begin(), jl_j.end(), in + o_jj);
+  std::copy(d->rot1_j, d->rot1_j + n1, in + o_rj);
+  int32_t *chan_grp = in + o_cg, *grp_off = in + o_go, *grp_list = in + o_gl;
+  for (int q = 0; q <= 2 * MMAX; ++q)
+    if (of_m[q] > 0) grp_off[grp_of[q] + 1] = (int32_t)of_m[q];
+  for (int g = 0; g < ng; ++g) grp_off[g + 1] += grp_off[g];
+  std::copy(grp_off, grp_off + ng, fillp.begin());
+  for (int n = 0; n < N; ++n) {
+    chan_grp[n] = grp_of[d->m[n] + MMAX];
+    grp_list[fillp[chan_grp[n]]++] = n;
+  }
+  // rows taken level by level ((j1, j2, j) of the row, then m): consecutive work
+  // items then read the same row of level factors
+  for (int n = 0; n < N; ++n) order[n] = n;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+    return chan_J[a] != chan_J[b] ? chan_J[a] < chan_J[b] : d->m[a] < d->m[b];
+  });
+  int32_t* work = in + o_wk;
+  for (int n : order)
+    for (int tile = 0; tile * (int64_t)256 < of_m[d->m[n] + MMAX]; ++tile) {
+      *work++ = n;
+      *work++ = tile;
+    }
   int32_t* di = (int32_t*)w;
   double* dd = (double*)(w + ibytes);
   double *db = dd, *dv = db + n_b, *dlf = dv + n_v, *dK = dlf + n_lf, *dF = dK + n_K,
@@ -2094,14 +2109,10 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
     return early ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream)
                  : hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
   };
-  if ((e = up(di, ints.data(), ints.size() * 4)) == hipSuccess &&
+  if ((e = up(di, in, n_ints * 4)) == hipSuccess &&
       (e = up(db, d->b, (size_t)n1 * bs * 8)) == hipSuccess)
-    e = up(dv, vs.data(), n_v * 8);
-  if (e != hipSuccess) {
-    if (early) (void)hipStreamSynchronize(c->stream);
-    hipFree(w);
-    return hip_fail(c, e, what);
-  }
+    e = up(dv, hold.vs.data(), n_v * 8);
+  if (e != hipSuccess) return drop(e);
   dev = CouplingDev{N, T, K, n1, nJ, bs, di + o_cJ, di + o_cr, di + o_cj, di + o_cm,
                     di + o_j1, di + o_j2, di + o_jj, di + o_rj, db, di + o_t1, di + o_tm,
                     di + o_t2, di + o_tl, di + o_tu, dv, dlf, dK, dF, di + o_cg, di + o_go,
@@ -2119,33 +2130,26 @@ mqct_status mqct_coupling_build(mqct_context* c, const mqct_coupling_desc* d, do
   CouplingDev dev;
   char* buf = nullptr;
   CouplingHold hold;
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  mqct_status st = coupling_setup(c, d, "coupling_build", dev, &buf, hold, [&](int N, int T, int K) {
-    // the outputs are cleared first: most elements stay zero, and the memory's write rate
-    // bounds it
-    const int64_t NN = (int64_t)N * N;
-    e0 = c->prof.next();
-    e1 = c->prof.next();
+  // the outputs are cleared first: most elements stay zero, and the memory's write rate
+  // bounds it
+  auto clear = [&]() {
+    const int64_t NN = (int64_t)d->N * d->N;
+    hipEvent_t e0 = c->prof.next(), e1 = c->prof.next();
     prof_mark(&c->prof, e0, c->stream);
-    hipError_t e = M_out ? launch_coupling_zero(M_out, K * NN, c->stream) : hipSuccess;
-    if (e == hipSuccess && G_out) e = launch_coupling_zero(G_out, T * NN, c->stream);
-    return e;
-  });
-  if (st != MQCT_OK) {
+    hipError_t e = M_out ? launch_coupling_zero(M_out, d->K * NN, c->stream) : hipSuccess;
+    if (e == hipSuccess && G_out) e = launch_coupling_zero(G_out, d->T * NN, c->stream);
     prof_mark(&c->prof, e1, c->stream);
-    return st;
-  }
-  hipError_t e = launch_coupling(dev, M_out, G_out, c->stream);
-  prof_mark(&c->prof, e1, c->stream);
-  if (e == hipErrorInvalidValue) {
-    (void)hipStreamSynchronize(c->stream);
-    hipFree(buf);
-    return fail(c, MQCT_ERR_ARG, "coupling_build: output too large for one launch");
-  }
+    return e;
+  };
+  mqct_status st = coupling_setup(c, d, "coupling_build", dev, &buf, hold, M_out, G_out, clear);
+  if (st != MQCT_OK) return st;
+  hipError_t e = launch_coupling(dev, M_out, G_out, &c->prof, c->stream);
   if (e == hipSuccess && c->prof.on)
     c->prof.bytes += ((M_out ? (double)dev.K : 0.0) + (G_out ? (double)dev.T : 0.0)) * dev.N *
                      (double)dev.N * 8.0;
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  // waited for on failure too: the uploads read `hold`, and the outputs are the caller's
+  const hipError_t es = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) e = es;
   hipFree(buf);
   if (e != hipSuccess) return hip_fail(c, e, "coupling_build");
   return MQCT_OK;
@@ -2168,7 +2172,7 @@ mqct_status mqct_coupling_build_sparse(mqct_context* c, const mqct_coupling_desc
   CouplingDev dev;
   char* buf = nullptr;
   CouplingHold hold;
-  mqct_status st = coupling_setup(c, d, "coupling_build_sparse", dev, &buf, hold);
+  mqct_status st = coupling_setup(c, d, "coupling_build_sparse", dev, &buf, hold, false, false);
   if (st != MQCT_OK) return st;
   // screening coefficients in the sorted term order, and the kept-element counter
   std::vector<double> vs((size_t)dev.T * n_screen);
@@ -2260,7 +2264,7 @@ mqct_status mqct_profile_read(mqct_context* c, double* total_ms, int64_t* launch
     float ms = 0.f;
     HIP_TRY(c, hipEventElapsedTime(&ms, c->prof.ev[i], c->prof.ev[i + 1]), "profile_read");
     tot += ms;
-    ++n;
+    if (!c->prof.joins(i)) ++n;
   }
   *total_ms = tot;
   *launches = n;

@@ -461,28 +461,38 @@ hipError_t launch_factors(const CouplingDev& d, hipStream_t s) {
   cpl_rotor<<<(unsigned)((nr + 255) / 256), 256, 0, s>>>(d);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t nj = (int64_t)d.T * d.nJ * d.nJ;
-  if ((nj + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
   cpl_jlevel<<<(unsigned)((nj + JL_ITEMS - 1) / JL_ITEMS), 256, 0, s>>>(d);
   return hipGetLastError();
 }
 
 }  // namespace
 
+bool coupling_launchable(int64_t N, int64_t T, int64_t K, int64_t n1, int64_t nJ, bool M, bool G) {
+  // as doubles: the products may pass 2^63
+  const double lim = 256.0 * 0x7fffffff, NN = (double)N * N;
+  return (!M || NN * K / 2 <= lim) && (!G || NN * T / 2 <= lim) && (double)T * n1 * n1 <= lim &&
+         (double)T * nJ * nJ <= lim;
+}
+
 hipError_t launch_coupling_zero(double* p, int64_t n, hipStream_t s) {
   const int64_t blocks = ((n + 1) / 2 + 255) / 256;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   cpl_zero<<<(unsigned)blocks, 256, 0, s>>>(p, n);
   return hipGetLastError();
 }
 
-hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, hipStream_t s) {
+hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, Prof* prof,
+                           hipStream_t s) {
   const size_t lds = (FILL_TC * FILL_LD + (size_t)(d.cg_jmax + 1) * (d.cg_lmax + 1)) * 8;
   hipError_t e = hipSuccess;
   if (lds > 65536) e = hipFuncSetAttribute((const void*)cpl_fill,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess || (e = launch_factors(d, s)) != hipSuccess) return e;
   const int64_t blocks = (d.n_work + NXCD - 1) / NXCD * NXCD;
+  if (prof) prof->join();      // one timed launch with the clearing of the outputs
+  hipEvent_t e0 = prof ? prof->next() : nullptr, e1 = prof ? prof->next() : nullptr;
+  prof_mark(prof, e0, s);
   cpl_fill<<<(unsigned)blocks, FILL_BLOCK, lds, s>>>(d, M, G);
+  prof_mark(prof, e1, s);
   return hipGetLastError();
 }
 

@@ -99,6 +99,7 @@ struct Prof {
   bool on = false;
   std::vector<hipEvent_t> ev;   // start/stop pairs
   size_t used = 0;
+  std::vector<size_t> joined;   // pairs that belong to the launch timed by the pair before
   double bytes = 0.0;           // host-known algorithmic bytes
   unsigned long long* slots = nullptr;   // pinned, device-filled knot counts
   std::vector<double> slot_bytes;        // bytes per counted knot of each used slot
@@ -113,6 +114,15 @@ struct Prof {
     }
     return ev[used++];
   }
+  // the next pair adds to the time of the pair before it and counts no launch of its own
+  void join() {
+    if (on) joined.push_back(used);
+  }
+  bool joins(size_t i) const {
+    for (size_t q : joined)
+      if (q == i) return true;
+    return false;
+  }
   // a pinned slot for a device-side count of occupied knots (null when off / full)
   unsigned long long* knot_slot(double bytes_per_knot) {
     if (!on) return nullptr;
@@ -126,6 +136,7 @@ struct Prof {
   }
   void reset() {
     used = 0;
+    joined.clear();
     bytes = 0.0;
     slot_bytes.clear();
   }
@@ -373,11 +384,15 @@ hipError_t launch_xs_rates(int nE, int L, int nT, const double* U, const double*
                            const double* g, const double* sym, double mu, const double* beta,
                            double* k, hipStream_t s);
 
+// whether the builder's launches for these sizes stay within the grid limits (M, G: outputs
+// asked for)
+bool coupling_launchable(int64_t N, int64_t T, int64_t K, int64_t n1, int64_t nJ, bool M, bool G);
 // n doubles set to zero
 hipError_t launch_coupling_zero(double* p, int64_t n, hipStream_t s);
 // coupling-matrix build: M [K][N][N] and/or G [T][N][N] (device, cleared before, either
 // may be null)
-hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, hipStream_t s);
+hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, Prof* prof,
+                           hipStream_t s);
 // screened build: factors, then the equal-m elements whose largest |M| over the
 // S screening radii (coefficients vs [T][S], sorted term order) exceeds thr,
 // counted in *count and listed in rows / cols up to capacity; then their values
