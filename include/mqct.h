@@ -446,7 +446,8 @@ mqct_status mqct_adjoint(mqct_context* ctx, const mqct_batch_desc* batch, int32_
  *                          work-list compaction is captured once per grid size as
  *                          a HIP graph and replayed; 0: launched one by one.
  *   MQCT_OPT_AUTOTUNE      1 (default): the first batch of each (storage type,
- *                          padded N, integrator) class times the candidate
+ *                          padded N, integrator, stored rows) class times the
+ *                          candidate
  *                          workgroup shapes (64..512 threads, fewest rows per lane
  *                          covering N) on a copy of up to 2048 of its
  *                          trajectories and keeps the fastest for the context;
@@ -454,7 +455,9 @@ mqct_status mqct_adjoint(mqct_context* ctx, const mqct_batch_desc* batch, int32_
  *                          The autotuner also times shared-stream shapes (a
  *                          thread per row, 4 or 8 waves that share out the
  *                          stored rows) against that choice on up to 320
- *                          trajectories; if one wins, the class switches to it
+ *                          trajectories, once for batches of at most one
+ *                          trajectory per compute unit and once for larger
+ *                          ones; if one wins, the class switches to it
  *                          once its active count falls to twice the number of
  *                          compute units (the latency-bound tail of a batch;
  *                          adaptive classes of at most 16 columns never switch).
@@ -485,9 +488,10 @@ enum { MQCT_OPT_GRAPHS = 1, MQCT_OPT_AUTOTUNE = 2, MQCT_OPT_CHUNK = 3, MQCT_OPT_
        MQCT_OPT_TAIL = 5, MQCT_OPT_COL_WORKSPACE = 6, MQCT_OPT_PER_LAUNCH = 7 };
 mqct_status mqct_set_option(mqct_context* ctx, int32_t option, int64_t value);
 /* The shapes chosen so far, as JSON text: one object per class with dtype,
- * npad, method (0 RK4, 1 DP5), block, rows_per_lane, tuned, the candidates'
- * milliseconds per step launch, and the tail shape (or null) with its
- * candidates' timings.  Valid until the next call on ctx. */
+ * npad, method (0 RK4, 1 DP5), rows (stored rows per evaluation, the next power
+ * of two), wide (batches of more trajectories than compute units), block,
+ * rows_per_lane, tuned, the candidates' milliseconds per step launch, and the
+ * tail shape (or null) with its candidates' timings.  Valid until the next call on ctx. */
 const char* mqct_tuning_report(mqct_context* ctx);
 
 /*

@@ -1084,7 +1084,11 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
       std::vector<std::pair<double, int64_t>> cost;
       for (int64_t b : kv.second) cost.push_back({-cost_of(b), b});
       std::stable_sort(cost.begin(), cost.end());
-      QueueClass qc{kv.first.first, kv.first.second, (int64_t)sorted.size(), (int64_t)cost.size()};
+      QueueClass qc{kv.first.first, kv.first.second, (int64_t)sorted.size(), (int64_t)cost.size(), 0};
+      for (int64_t b : kv.second) {
+        const DevSystem& sy = c->systems[c->h_traj[b].sys].dev;
+        qc.rows = std::max(qc.rows, sy.ell_w > 0 ? sy.ell_w : sy.N);
+      }
       for (auto& pr : cost) sorted.push_back(c->h_traj[pr.second]);
       classes.push_back(qc);
     }
@@ -1827,14 +1831,14 @@ mqct_status mqct_set_option(mqct_context* c, int32_t option, int64_t value) {
 const char* mqct_tuning_report(mqct_context* c) {
   if (!c) return "";
   std::string r = "[";
-  char buf[256];
+  char buf[512];
   for (size_t i = 0; i < c->qcache.entries.size(); ++i) {
     const QueueTuneEntry& en = c->qcache.entries[i];
     const QKernelSet& ks = queue_kernels(en.dtype)[en.shape];
     snprintf(buf, sizeof buf,
-             "%s{\"dtype\": %d, \"npad\": %d, \"method\": %d, \"block\": %d, \"rows_per_lane\": %d, "
-             "\"tuned\": %s, \"candidates\": [",
-             i ? ", " : "", en.dtype, en.npad, en.method, ks.block, ks.rpt * (en.dtype == C128 ? 1 : 2),
+             "%s{\"dtype\": %d, \"npad\": %d, \"method\": %d, \"rows\": %d, \"wide\": %s, "
+             "\"block\": %d, \"rows_per_lane\": %d, \"tuned\": %s, \"candidates\": [",
+             i ? ", " : "", en.dtype, en.npad, en.method, en.rows, en.wide ? "true" : "false", ks.block, ks.rpt * (en.dtype == C128 ? 1 : 2),
              en.tuned ? "true" : "false");
     r += buf;
     for (size_t j = 0; j < en.ms.size(); ++j) {

@@ -271,6 +271,7 @@ constexpr int QUEUE_SHAPES = 13;
 struct QueueClass {
   int dtype, npad;
   int64_t first, n;    // records [first, first + n) of the device record array
+  int rows;            // most stored rows (slots) of its systems
 };
 
 struct QueueOpts {
@@ -283,9 +284,15 @@ struct QueueOpts {
   int64_t col_ws = 0;  // columns schedule: workspace cap in bytes (0: 80 % of free memory)
 };
 
-// Autotuner decisions, kept for the life of a context.
+// Autotuner decisions, kept for the life of a context.  What a trajectory streams is
+// part of the key (a 36-slot sparse class and a dense one differ sevenfold at N = 256),
+// and so is whether the batch holds more trajectories than the device has compute units:
+// the tail shape depends on whether one or two share a unit.
 struct QueueTuneEntry {
-  int dtype, npad, method, shape;
+  int dtype, npad, method;
+  int rows;                                 // stored rows per evaluation, the next power of two
+  bool wide;                                // more trajectories than compute units
+  int shape;
   bool tuned;
   std::vector<std::pair<int, double>> ms;   // candidate shape -> ms per step launch
   int tail_shape = -1;                      // shape once few trajectories remain (-1: same)

@@ -14,16 +14,18 @@
 //         Npad, lanes within a factor two of the rows), timed after the batch's
 //         init on a copy of the state of up to TUNE_SAMPLE trajectories;
 //   tail  the shared-stream shapes (4 or 8 waves that share out the stored rows)
-//         and the bulk choice, timed on a copy of TAIL_SAMPLE trajectories -- between
-//         one and two per compute unit, as the tail starts: a shape of which only one
-//         workgroup fits a unit is two rounds there.  (On 32 trajectories the 512-
-//         thread shape won by 43 to 46 us per attempt at N = 256 and then took 86 of
-//         the 59 us that 321 trajectories need: 6.6 s instead of 5.4 for the uneven
-//         workload.)  If a shared-stream shape wins, the class
-//         switches to it once its active count drops to twice the number of
-//         compute units.  (The smallest adaptive classes do not: TAIL_MIN_NPAD.)
+//         and the bulk choice, timed on a copy of up to TAIL_SAMPLE trajectories --
+//         between one and two per compute unit, as the tail of a large batch starts: a
+//         shape of which only one workgroup fits a unit is two rounds there.  (On 32
+//         trajectories the 512-thread shape won by 43 to 46 us per attempt at N = 256
+//         and then took 86 us where 59 are enough for 321 trajectories: 6.6 s instead
+//         of 5.4 for the uneven workload.)  Batches of at most one trajectory per unit
+//         have a choice of their own for the same reason.  If a shared-stream shape
+//         wins, the class switches to it once its active count drops to twice the
+//         number of compute units.  (The smallest adaptive classes do not:
+//         TAIL_MIN_NPAD.)
 // Each candidate is timed in two passes of two step launches (results are not
-// written); the choices are kept for the context.
+// written); the choices are kept for the context (QueueTuneEntry has the key).
 #include "shared.h"
 
 #include <algorithm>
@@ -255,26 +257,39 @@ hipError_t run_queue(const DevSystem* d_systems, const TrajIn* d_traj,
   };
   auto lds_of = [&](const ClassRun& r, int shape) { return shape_lds(r.c.dtype, r.c.npad, shape); };
 
-  // shapes: cached decision, else default (and tuned after init)
+  // shapes: cached decision, else default (and tuned after init).  The bulk shape is
+  // shared by the wide and the narrow entry of a class.
   std::vector<size_t> to_tune;
   for (size_t k = 0; k < runs.size(); ++k) {
     ClassRun& r = runs[k];
-    bool found = false;
-    for (size_t q = 0; q < cache.entries.size(); ++q) {
-      const QueueTuneEntry& en = cache.entries[q];
-      if (en.dtype == r.c.dtype && en.npad == r.c.npad && en.method == method) {
-        r.shape = en.shape;
-        r.tail_shape = en.tail_shape;
+    int rows = 1;
+    while (rows < r.c.rows) rows *= 2;
+    const bool wide = r.c.n > cus;
+    bool found = false, bulk = false;
+    QueueTuneEntry en{r.c.dtype, r.c.npad, method, rows, wide, -1, false, {}};
+    for (size_t q = 0; q < cache.entries.size() && !found; ++q) {
+      const QueueTuneEntry& o = cache.entries[q];
+      if (o.dtype != en.dtype || o.npad != en.npad || o.method != method || o.rows != rows) continue;
+      if (o.wide == wide) {
+        r.shape = o.shape;
+        r.tail_shape = o.tail_shape;
         r.entry = q;
         found = true;
+      } else {
+        en.shape = o.shape;
+        en.tuned = o.tuned;
+        en.ms = o.ms;
+        bulk = true;
       }
     }
     if (found) continue;
-    const std::vector<int> cand = candidates(r.c.dtype, r.c.npad, method, false);
-    if (cand.empty()) return hipErrorInvalidValue;
-    const int def = default_shape(r.c.dtype, r.c.npad);
-    r.shape = std::find(cand.begin(), cand.end(), def) != cand.end() ? def : cand.back();
-    QueueTuneEntry en{r.c.dtype, r.c.npad, method, r.shape, false, {}};
+    if (!bulk) {
+      const std::vector<int> cand = candidates(r.c.dtype, r.c.npad, method, false);
+      if (cand.empty()) return hipErrorInvalidValue;
+      const int def = default_shape(r.c.dtype, r.c.npad);
+      en.shape = std::find(cand.begin(), cand.end(), def) != cand.end() ? def : cand.back();
+    }
+    r.shape = en.shape;
     r.entry = cache.entries.size();
     cache.entries.push_back(en);
     if (opt.tune) to_tune.push_back(k);
@@ -341,7 +356,7 @@ hipError_t run_queue(const DevSystem* d_systems, const TrajIn* d_traj,
     QueueTuneEntry& en = cache.entries[r.entry];
     const std::vector<int> cand = candidates(r.c.dtype, r.c.npad, method, false);
     std::vector<double> best;
-    if (cand.size() > 1) {
+    if (cand.size() > 1 && !en.tuned) {
       if ((e = time_shapes(r, std::min(r.c.n, TUNE_SAMPLE), cand, best)) != hipSuccess) return e;
       size_t bi = 0;
       for (size_t ci = 1; ci < cand.size(); ++ci)
