@@ -461,9 +461,13 @@ mqct_status mqct_adjoint(mqct_context* ctx, const mqct_batch_desc* batch, int32_
  *                          once its active count falls to twice the number of
  *                          compute units (the latency-bound tail of a batch;
  *                          adaptive classes of at most 16 columns never switch).
+ *                          A switch changes the order of sums: whole collisions
+ *                          amplify that to between 1e-10 and 5e-7 of a final
+ *                          amplitude in the most sensitive trajectories.
  *   MQCT_OPT_CHUNK         step launches per replay (1..4096, default 16).
  *   MQCT_OPT_RESET_TUNING  forget the shapes chosen so far (value ignored).
- *   MQCT_OPT_TAIL          1 (default): use the tuned tail shape; 0: never switch;
+ *   MQCT_OPT_TAIL          1 (default): use the tuned tail shape; 0: never switch
+ *                          (one order of sums from the first step to the last);
  *                          2: run every class on its widest shared-stream shape from
  *                          the first step (for testing that form).
  *   MQCT_OPT_PER_LAUNCH    attempts (RK4 steps, DP5 attempts) of a trajectory per

@@ -23,7 +23,7 @@
 //         have a choice of their own for the same reason.  If a shared-stream shape
 //         wins, the class switches to it once its active count drops to twice the
 //         number of compute units.  (The smallest adaptive classes do not:
-//         TAIL_MIN_NPAD.)
+//         TAIL_FIXED_NPAD.)
 // Each candidate is timed in two passes of two step launches (results are not
 // written); the choices are kept for the context (QueueTuneEntry has the key).
 #include "shared.h"
@@ -52,13 +52,17 @@ namespace {
 
 constexpr int64_t TUNE_SAMPLE = 2048;
 constexpr int64_t TAIL_SAMPLE = 320;
-// Adaptive classes of at most this many columns keep their bulk shape to the end.  Whole
-// collisions of a rotor with so few channels (N = 9 and 16, 150 to 2000 cm^-1) carry a
-// change in the order of a sum from 1e-16 to between 2e-9 and 3e-7 of the final state, so
-// the last trajectories of a batch are stepped as the others are, at 1.6 to 1.8 times the
-// shared-stream form's time (66 trajectories, N = 16: 6.8 and 4.2 ms).  N = 81 and 256
-// carry it to 1e-10 at most.
-constexpr int TAIL_MIN_NPAD = 17;
+// Adaptive classes of at most this many padded columns (N <= 16) keep their bulk shape to
+// the end, at 1.6 to 1.8 times the shared-stream form's time (66 trajectories, N = 16: 6.8
+// and 4.2 ms).  This is not for speed: a whole collision amplifies a change in the order of
+// a sum, 1e-16, by what the collision itself is sensitive to.  Largest change of a final
+// amplitude between the two forms, 600 collisions of 150 to 2000 cm^-1 each, rotor + atom:
+// 5e-7 at N = 9, 2e-8 at 16, 2e-9 at 25, 7e-8 at 36, 2e-8 at 49, 7e-10 at 64, 2e-9 at 81;
+// two rotors 4e-10 at 16, 1e-10 at 81 and 256.  From N = 25 on the tail's shape has always
+// been the timed one, so results carry that spread from one choice to another; below it
+// one order of sums ran throughout, and still does.  MQCT_OPT_TAIL = 0 gives that at every
+// size.
+constexpr int TAIL_FIXED_NPAD = 16;
 constexpr size_t LDS_MAX = 160 * 1024;
 constexpr int CT = 1024;   // threads of the compaction kernel
 
@@ -367,7 +371,7 @@ hipError_t run_queue(const DevSystem* d_systems, const TrajIn* d_traj,
       for (size_t ci = 0; ci < cand.size(); ++ci) en.ms.push_back({cand[ci], best[ci]});
     }
     std::vector<int> tc = candidates(r.c.dtype, r.c.npad, method, true);
-    if (!tc.empty() && (method == 0 || r.c.npad >= TAIL_MIN_NPAD)) {
+    if (!tc.empty() && (method == 0 || r.c.npad > TAIL_FIXED_NPAD)) {
       tc.push_back(r.shape);
       if ((e = time_shapes(r, std::min(r.c.n, TAIL_SAMPLE), tc, best)) != hipSuccess) return e;
       size_t bi = 0;
