@@ -69,13 +69,20 @@ enum {
   MQCT_T_BELOW_GRID = 8,      /* R went below the first knot (linear continuation used) */
   MQCT_T_NONFINITE = 16       /* NaN/Inf appeared; the trajectory was stopped          */
 };
-/* batch schedules */
+/* batch schedules.  MQCT_SCHED_AUTO takes COLUMNS for coordinate-list systems and QUEUE
+ * for DP5 (with large dense systems' shares on BINNED).  Fixed steps run on the kernels of
+ * GEMV, except that
+ *   - a batch of one dense FP64 system with large tables or many trajectories runs on
+ *     BINNED (chosen by N, K, storage type and B; not from 2^31 steps on).  Without room
+ *     for the first size of a pass it runs in smaller passes, with the same bits; without
+ *     room for 64 trajectories, on GEMV;
+ *   - the trajectories of one storage type run in a form of GEMV for small batches if they
+ *     are at most two per compute unit (one, where the form needs 512 threads and gains
+ *     nothing at two) and their tables' slices are small together.
+ * The forms differ in the order of their sums only, so a trajectory's rounding depends on
+ * the batch around it; step counts do not enter.  GEMV is one order for every batch. */
 enum {
-  MQCT_SCHED_AUTO = 0,        /* library chooses: GEMV for fixed steps, BINNED where a
-                                 single FP64 dense system has large tables or many
-                                 trajectories (by N, K and B alone), QUEUE for DP5
-                                 (with large dense systems' shares on BINNED), COLUMNS
-                                 for coordinate-list systems                         */
+  MQCT_SCHED_AUTO = 0,        /* library chooses (above)                                */
   MQCT_SCHED_GEMV = 1,        /* one workgroup per trajectory, step loop inside a kernel */
   MQCT_SCHED_BINNED = 2,      /* lockstep stages, trajectories binned by spline knot,
                                  table x amplitude-columns products on matrix cores;
@@ -245,7 +252,9 @@ mqct_status mqct_system_free(mqct_context* ctx, int32_t system_id);
  *                    the store; init_channel, a0, classical0, E_coll, b, R0, t0
  *                    and dt are then ignored.  RK4 takes n_steps[b] further
  *                    steps of the stored h at t = t_origin + (n_origin + j) h, so
- *                    that a run split in two equals the whole run bit for bit;
+ *                    that a run split in two equals the whole run bit for bit
+ *                    (on MQCT_SCHED_AUTO too, unless device memory is short for
+ *                    64 trajectories in one of the calls and not in the other);
  *                    DP5 continues with the stored step size, rejection flag
  *                    and counts (max_steps bounds the total), re-evaluating the
  *                    first stage at the stored state (first same as last), and

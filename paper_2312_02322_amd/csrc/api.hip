@@ -166,15 +166,21 @@ mqct_status ensure(mqct_context* c, DevBuf& b, size_t bytes, const char* what) {
 //    binned, complex tables: N = 969, K = 200, B = 1024 8.1 -> 1.2 ms; N = 256, K = 1000,
 //    B = 1024 687 -> 360 us; N = 160, K = 200, B = 1024 239 -> 101 us.  Below: N = 256,
 //    K = 1000, B = 256 (1.07 GB) 190 -> 217 us; N = 100, K = 200, B = 512 (0.34 GB)
-//    50 -> 48 us.  Slices of 1.2 MB, because lockstep ends with the longest trajectory:
-//    one alone takes 29 -> 40 us an evaluation at complex N = 160, 12 -> 25 at N = 49;
+//    50 -> 48 us.  Slices of 1.2 MB, because the few trajectories that outlast a batch
+//    walk faster alone than in lockstep: one takes 12 -> 25 us an evaluation at complex
+//    N = 49, 26 -> 36 at N = 160, 47 -> 49 at N = 256 (sixteen: 54 -> 39 at N = 160, 128:
+//    60 -> 64).  Whole ragged batches of 1024, per-trajectory -> binned: collisions of 100
+//    to 2000 cm^-1 (lengths 1 to 4.5) complex N = 160 49 -> 25 ms, N = 256 117 -> 40; eight
+//    trajectories 30 times the others' length N = 160 43 -> 25; one of 30 times 20 -> 23,
+//    one of 100 times 23 -> 30;
 //  - or a slice set so large that one workgroup walks it for longer than the lockstep
 //    stage's launches take and the few rows of a small batch leave the device idle:
 //    8 MB and at most 64 trajectories, or 24 MB.  K = 1000, each trajectory on knots of
 //    its own: real N = 512 (8.4 MB) B = 1 93 -> 55 us, B = 64 158 -> 118 us, B = 128
 //    186 -> 220; complex N = 640 (26 MB) B = 1 458 -> 103, B = 256 991 -> 941 us; below
 //    8 MB, real N = 400 (5.1 MB): B = 1 60 -> 48 us, B = 128 143 -> 154.
-// The step counts do not enter: a run in two calls takes the same route in both.
+// The step counts do not enter (but for 2^31, which the binned counters do not hold): a
+// run in two calls takes the same route in both and has the bits of the run in one.
 bool auto_binned(const DevSystem& sy, const TrajIn* t, int64_t B) {
   if ((sy.dtype != C128 && sy.dtype != R64) || sy.ell_w > 0 || sy.Npad > 4096) return false;
   for (int64_t b = 0; b < B; ++b)
@@ -1145,8 +1151,9 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
   out.state = (mqct_traj_state*)c->st_rec.p;
   out.st_amp = (double2*)c->st_amp.p;
 
-  // fixed steps on the binned schedule: asked for, or the library's choice (without
-  // room for its workspace the per-trajectory schedule stands)
+  // fixed steps on the binned schedule: asked for, or the library's choice.  Without room
+  // for its workspace that one runs in smaller passes, a trajectory's bits being the same
+  // in each; the per-trajectory schedule stands where there is no room for 64.
   bool rk4_binned = binned && !dp5;
   int64_t bin_n = B;      // trajectories per pass
   if (rk4_binned) {
@@ -1160,10 +1167,11 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
     bin_n = std::min<int64_t>(B, 1 << 20);
     while (bin_n > 64 && need(bin_n) > AUTO_BINNED_WS) bin_n = (bin_n + 1) / 2;
     const std::string err = c->err;
-    rk4_binned = ensure(c, c->binws, need(bin_n), "run: binned workspace") == MQCT_OK;
-    if (!rk4_binned) {
+    while (!(rk4_binned = ensure(c, c->binws, need(bin_n), "run: binned workspace") == MQCT_OK)) {
       c->err = err;
       (void)hipGetLastError();
+      if (bin_n <= 64) break;
+      bin_n = (bin_n + 1) / 2;
     }
   }
   if (columns) {
