@@ -80,7 +80,8 @@ enum {
  *     are at most two per compute unit (one, where the form needs 512 threads and gains
  *     nothing at two) and their tables' slices are small together.
  * The forms differ in the order of their sums only, so a trajectory's rounding depends on
- * the batch around it; step counts do not enter.  GEMV is one order for every batch. */
+ * the batch around it; step counts do not enter.  GEMV's order depends on the largest
+ * padded N of the storage type alone. */
 enum {
   MQCT_SCHED_AUTO = 0,        /* library chooses (above)                                */
   MQCT_SCHED_GEMV = 1,        /* one workgroup per trajectory, step loop inside a kernel */

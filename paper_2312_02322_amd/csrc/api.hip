@@ -1247,16 +1247,17 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
                            dtype_bytes(sy.dtype);
         }
       }
-      // A small batch left to the library runs in the shared-stream form: at most two
-      // trajectories per compute unit, and so few slice bytes per evaluation that the
-      // caches' latency and not their bandwidth sets the time.  N = 49 FP64, 100 steps:
+      // A small batch left to the library runs in the shared-stream form: one or two
+      // trajectories per compute unit (shared_rk4_most), and so few slice bytes per
+      // evaluation that the caches' latency and not their bandwidth sets the time.  N = 49 FP64, 100 steps:
       // 3.0 -> 1.56 ms at 64 trajectories, 3.6 -> 2.1 at 512, no gain at 768 (4.06 and
       // 3.5) and 1024; N = 256: 537 MB per evaluation (256 dense trajectories) 11.5
       // ms either way, 747 MB (N = 300 complex) 1.15 -> 1.26, 134 MB 16.5 -> 11.5.
       double slices = 0.0;
       for (int64_t q = ranges[d].first; q < ranges[d].second; ++q)
         slices += 4.0 * (double)c->systems[c->h_traj[q].sys].dev.knot_stride * dtype_bytes(d);
-      const bool shared = bd->schedule == MQCT_SCHED_AUTO && n <= 2 * (int64_t)c->n_cu &&
+      const bool shared = bd->schedule == MQCT_SCHED_AUTO &&
+                          n <= shared_rk4_most(d, max_npad[d], c->n_cu) &&
                           slices <= SHARED_MAX_BYTES;
       hipError_t e = launch_rk4_gemv(c->d_systems, (const TrajIn*)c->traj.p + ranges[d].first, n,
                                      d_a0, out, d, max_npad[d], c->stream, &c->prof, shared);

@@ -117,8 +117,9 @@ rk4_gemv_kernel(const DevSystem* __restrict__ systems, const TrajIn* __restrict_
   Kern<DT, BLOCK, RPT>::run_rk4(sy, tj, a0_all, out, lds);
 }
 
-// The same in the shared-stream form (shared.h), for batches of at most two
-// trajectories per compute unit (two workgroups per unit: at most 256 registers).
+// The same in the shared-stream form (shared.h), for small batches (shared_rk4_most).  At
+// least two waves per SIMD: at most 256 registers, so that two workgroups of 256 threads,
+// or one of 512, share a compute unit.
 template <int DT, int BLOCK>
 __global__ void __launch_bounds__(BLOCK, 2)
 rk4_shared_kernel(const DevSystem* __restrict__ systems, const TrajIn* __restrict__ trajs,
@@ -187,6 +188,23 @@ hipError_t launch_dt(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n
 }
 
 }  // namespace
+
+// Most trajectories of a launch that gain from the shared-stream form: two per compute unit
+// where 256 threads hold the rows.  With 512 threads only one workgroup fits a unit, and
+// the second round costs more than the form gives, except with FP32 tables or at least
+// three shares.  Microseconds per evaluation, row-split -> shared, sparse tables, at 256,
+// 257 and 512 trajectories: FP64 two shares, complex N = 250 14.4 -> 12.3, 15.0 -> 16.9,
+// 21.6 -> 23.3, real N = 512 15.4 -> 12.3, 16.0 -> 18.4, 22.4 -> 23.3; three shares,
+// complex N = 160 12.0 -> 6.8, 12.5 -> 11.0, 14.0 -> 12.5, real N = 300 22.9 -> 14.0,
+// 24.1 -> 21.2, 27.6 -> 26.8; FP32 two shares, complex N = 500 12.8 -> 12.1, 20.1 -> 18.7,
+// 24.6 -> 23.2.
+int64_t shared_rk4_most(int dtype, int max_npad, int n_cu) {
+  const bool fp32 = dtype_fp32(dtype);
+  const int vec = dtype == C128 ? 1 : 2;
+  if (shared::fits(max_npad, vec, 256)) return 2 * (int64_t)n_cu;
+  if (!shared::fits(max_npad, vec, 512)) return 0;
+  return fp32 || 512 / (max_npad / vec) >= 3 ? 2 * (int64_t)n_cu : n_cu;
+}
 
 hipError_t launch_rk4_gemv_t(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                              const double* d_a0, TrajOut out, int dtype, int max_npad,

@@ -211,6 +211,8 @@ hipError_t launch_spline_prepare(const double* M_in, const double* R, int N, int
 hipError_t launch_rk4_gemv(const DevSystem* d_systems, const TrajIn* d_traj, int64_t n_traj,
                            const double* d_a0, TrajOut out, int dtype, int max_npad,
                            hipStream_t s, Prof* prof = nullptr, bool shared_form = false);
+// Most trajectories of one storage type that gain from the shared-stream form.
+int64_t shared_rk4_most(int dtype, int max_npad, int n_cu);
 
 // Adaptive-step controls.
 struct DpCtl {

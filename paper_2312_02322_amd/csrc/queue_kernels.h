@@ -691,8 +691,7 @@ void fill_one(QKernelSet& ks) {
       nullptr;
   if constexpr (qshape_shared(K)) {
     // a class is initialised with its row-split shape; one attempt per launch always
-    // (a loop of attempts would hold more registers than two workgroups per compute
-    // unit have)
+    // (a loop of attempts would hold more registers than two waves per SIMD have)
     ks.step[0] = ks.step_multi[0] = (const void*)q_step_shared<DT, BL, 0>;
     ks.step[1] = ks.step_multi[1] = (const void*)q_step_shared<DT, BL, 1>;
   } else if constexpr (BL * RP * Tr<DT>::VEC <= 4096) {
