@@ -21,8 +21,16 @@ using namespace mqct;
 
 namespace {
 
-// Shared-stream form: most slice bytes per evaluation of the whole batch (mqct_run).
-constexpr double SHARED_MAX_BYTES = 320e6;
+// Shared-stream form: most slice bytes per evaluation of the whole batch (mqct_run).  With
+// more than one trajectory per compute unit and dense tables whose row-split kernel reads
+// two columns a thread the line is lower: the more knots the trajectories spread over, the
+// sooner bandwidth sets the time.  Row-split over shared time, dense real FP64 at 512
+// trajectories, K = 60 and 1000: N = 96 (151 MB) 1.71 and 1.01, N = 105 (193 MB) 1.42 and
+// 0.94, N = 121 (254 MB) 1.10 and 0.90; complex FP32 N = 112 (206 MB) 1.55 and 1.02, N = 144
+// at 420 and 460 (279 and 305 MB, K = 1000) 1.01 and 0.95, N = 160 at 300 (246 MB) 1.32 and
+// 0.94.  Sparse tables, complex FP64 and real FP32 gain up to the common line (sparse real
+// FP64 N = 250 273 MB 1.01; complex FP64 N = 112 305 MB 1.2; real FP32 N = 208 318 MB 1.0).
+constexpr double SHARED_MAX_BYTES = 320e6, SHARED_TWO_R64 = 160e6, SHARED_TWO_C64 = 220e6;
 // Workspace of one binned pass of a fixed-step batch on the default schedule; a larger
 // batch runs in several.
 constexpr size_t AUTO_BINNED_WS = (size_t)1 << 30;
@@ -1253,12 +1261,16 @@ mqct_status mqct_run(mqct_context* c, const mqct_batch_desc* bd, mqct_batch_resu
       // 3.0 -> 1.56 ms at 64 trajectories, 3.6 -> 2.1 at 512, no gain at 768 (4.06 and
       // 3.5) and 1024; N = 256: 537 MB per evaluation (256 dense trajectories) 11.5
       // ms either way, 747 MB (N = 300 complex) 1.15 -> 1.26, 134 MB 16.5 -> 11.5.
-      double slices = 0.0;
-      for (int64_t q = ranges[d].first; q < ranges[d].second; ++q)
-        slices += 4.0 * (double)c->systems[c->h_traj[q].sys].dev.knot_stride * dtype_bytes(d);
+      double slices = 0.0, most = SHARED_MAX_BYTES;
+      bool dense = false;
+      for (int64_t q = ranges[d].first; q < ranges[d].second; ++q) {
+        const DevSystem& sy = c->systems[c->h_traj[q].sys].dev;
+        slices += 4.0 * (double)sy.knot_stride * dtype_bytes(d);
+        dense |= sy.ell_w == 0;
+      }
+      if (dense && n > c->n_cu) most = d == R64 ? SHARED_TWO_R64 : d == C64 ? SHARED_TWO_C64 : most;
       const bool shared = bd->schedule == MQCT_SCHED_AUTO &&
-                          n <= shared_rk4_most(d, max_npad[d], c->n_cu) &&
-                          slices <= SHARED_MAX_BYTES;
+                          n <= shared_rk4_most(d, max_npad[d], c->n_cu) && slices <= most;
       hipError_t e = launch_rk4_gemv(c->d_systems, (const TrajIn*)c->traj.p + ranges[d].first, n,
                                      d_a0, out, d, max_npad[d], c->stream, &c->prof, shared);
       if (e == hipErrorInvalidValue)

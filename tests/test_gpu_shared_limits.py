@@ -53,6 +53,32 @@ def test_most_trajectories(gpu_lib, N, cplx, storage, per_unit):
     ctx.close()
 
 
+# dense tables: N, complex, storage, trajectories per compute unit above one (fraction),
+# shared-stream form?
+BYTES = [(121, False, "R64", 0.01, True), (121, False, "R64", 0.5, False),
+         (176, False, "R64", 0.0, True), (160, True, "C64", 0.01, True),
+         (160, True, "C64", 0.1, False), (112, True, "C128", 0.4, True)]
+
+
+@pytest.mark.parametrize("N,cplx,storage,more,shared", BYTES)
+def test_most_bytes(gpu_lib, N, cplx, storage, more, shared):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus != 256:
+        pytest.skip("the sizes are those of 256 compute units")
+    B = cus + int(more * cus)
+    print("[gpu] shared bytes N=%d %s B=%d" % (N, storage, B), flush=True)
+    s = banded(N, cplx, band=N)
+    ctx = gpu_lib.Context()
+    sid = ctx.load_system(R_grid=s.R, E=s.E, M=s.M, mu=s.mu, storage=storage)
+    kw = batch(s, B, 4)
+    a = ctx.run_host([sid] * B, [N] * B, **kw)["a_final"]
+    g = ctx.run_host([sid] * B, [N] * B, schedule="gemv", **kw)["a_final"]
+    ctx.close()
+    assert np.array_equal(a, g) != shared
+    assert np.max(np.abs(a - g)) < (1e-12 if storage in ("R64", "C128") else 1e-6)
+
+
 @pytest.mark.parametrize("schedule", ["auto", "queue"])
 @pytest.mark.parametrize("N,cplx,storage", [(9, False, "R64"), (49, True, "C64"), (140, True, "C128")])
 def test_blow_up(gpu_lib, N, cplx, storage, schedule):
