@@ -17,6 +17,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 namespace mqct {
 
 namespace {
@@ -47,6 +49,7 @@ constexpr double SER_Z = 5.0;
 // also without cancellation.  Long ones: mu_0 = 1 - e^{-z} and upward.
 __device__ __forceinline__ void rate_moments(double z, double e, const double* __restrict__ rcp,
                                              double (&mu)[5]) {
+  z = fmin(z, 1e4);       // e is 0 from 746 on; z^4 stays finite
   const double z2 = z * z, z3 = z2 * z, z4 = z2 * z2;
   if (z <= SER_Z) {
     double s = 1.0;
@@ -221,9 +224,9 @@ hipError_t launch_xs_rates(int nE, int L, int nT, const double* U, const double*
     if (e != hipSuccess) return e;
   }
   // grid.y: at most 65535 groups of RATE_TC temperatures per launch
-  const int tmax = 65535 * RATE_TC;
-  for (int t = 0; t < nT; t += tmax) {
-    const int m = nT - t < tmax ? nT - t : tmax;
+  const int64_t tmax = 65535 * RATE_TC;
+  for (int64_t t = 0; t < nT; t += tmax) {
+    const int m = (int)std::min<int64_t>(nT - t, tmax);
     xs_rate_kernel<<<dim3((unsigned)((n + RATE_BLOCK - 1) / RATE_BLOCK),
                           (unsigned)((m + RATE_TC - 1) / RATE_TC)),
                      RATE_BLOCK, lds, s>>>(nE, L, m, U, E, g, sym, mu, beta + t, k + t * n);
