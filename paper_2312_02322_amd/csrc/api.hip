@@ -2323,8 +2323,14 @@ mqct_status mqct_cross_sections(mqct_context* c, int32_t mem, int64_t B, int32_t
   HIP_TRY(c, hipSetDevice(c->device), "cross_sections");
   mqct_status st;
   const size_t lsz = (size_t)B * n_levels * 8, ssz = (size_t)n_levels * n_levels * 8;
+  const size_t n_list = (size_t)n_levels + 1 + N;
+  if ((st = ensure(c, c->xs[0], lsz + n_list * 4, "cross_sections")) != MQCT_OK) return st;
+  if (mem == MQCT_MEM_HOST &&
+      ((st = ensure(c, c->xs[1], (size_t)B * N * 8 + B * 8 + B * 4 + 64, "cross_sections")) != MQCT_OK ||
+       (st = ensure(c, c->xs[2], ssz, "cross_sections")) != MQCT_OK))
+    return st;
   // the channels of every level, ascending: offsets, then the channels
-  std::vector<int32_t> lists((size_t)n_levels + 1 + N, 0);
+  std::vector<int32_t> lists(n_list, 0);
   int32_t* chan = lists.data() + n_levels + 1;
   for (int n = 0; n < N; ++n) ++lists[level_of_channel[n] + 1];
   for (int l = 0; l < n_levels; ++l) lists[l + 1] += lists[l];
@@ -2332,35 +2338,33 @@ mqct_status mqct_cross_sections(mqct_context* c, int32_t mem, int64_t B, int32_t
     std::vector<int32_t> at(lists.begin(), lists.begin() + n_levels);
     for (int n = 0; n < N; ++n) chan[at[level_of_channel[n]]++] = n;
   }
-  if ((st = ensure(c, c->xs[0], lsz + lists.size() * 4, "cross_sections")) != MQCT_OK) return st;
   double* lsum = (double*)c->xs[0].p;
   int32_t* dlev = (int32_t*)((char*)c->xs[0].p + lsz);
-  HIP_TRY(c, hipMemcpyAsync(dlev, lists.data(), lists.size() * 4, hipMemcpyHostToDevice, c->stream),
-          "cross_sections");
+  hipError_t e = hipSuccess;
+  auto copy = [&](void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+    if (e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, kind, c->stream);
+  };
+  copy(dlev, lists.data(), n_list * 4, hipMemcpyHostToDevice);
   const double *dP = P, *db = b;
   const int32_t* dil = init_level;
   double* dsig = sigma;
   if (mem == MQCT_MEM_HOST) {
-    if ((st = ensure(c, c->xs[1], (size_t)B * N * 8 + B * 8 + B * 4 + 64, "cross_sections")) != MQCT_OK)
-      return st;
-    if ((st = ensure(c, c->xs[2], ssz, "cross_sections")) != MQCT_OK) return st;
     char* base = (char*)c->xs[1].p;
-    HIP_TRY(c, hipMemcpyAsync(base, P, (size_t)B * N * 8, hipMemcpyHostToDevice, c->stream), "cross_sections");
-    HIP_TRY(c, hipMemcpyAsync(base + (size_t)B * N * 8, b, B * 8, hipMemcpyHostToDevice, c->stream), "cross_sections");
-    HIP_TRY(c, hipMemcpyAsync(base + (size_t)B * N * 8 + B * 8, init_level, B * 4,
-                              hipMemcpyHostToDevice, c->stream), "cross_sections");
+    copy(base, P, (size_t)B * N * 8, hipMemcpyHostToDevice);
+    copy(base + (size_t)B * N * 8, b, B * 8, hipMemcpyHostToDevice);
+    copy(base + (size_t)B * N * 8 + B * 8, init_level, B * 4, hipMemcpyHostToDevice);
     dP = (const double*)base;
     db = (const double*)(base + (size_t)B * N * 8);
     dil = (const int32_t*)(base + (size_t)B * N * 8 + B * 8);
     dsig = (double*)c->xs[2].p;
   }
-  HIP_TRY(c, launch_xsec(B, N, dP, db, dil, dlev, dlev + n_levels + 1, n_levels, b_max, lsum, dsig,
-                         c->stream),
-          "cross_sections");
-  if (mem == MQCT_MEM_HOST) {
-    HIP_TRY(c, hipMemcpyAsync(sigma, dsig, ssz, hipMemcpyDeviceToHost, c->stream), "cross_sections");
-  }
-  HIP_TRY(c, hipStreamSynchronize(c->stream), "cross_sections");
+  if (e == hipSuccess)
+    e = launch_xsec(B, N, dP, db, dil, dlev, dlev + n_levels + 1, n_levels, b_max, lsum, dsig,
+                    c->stream);
+  if (mem == MQCT_MEM_HOST) copy(sigma, dsig, ssz, hipMemcpyDeviceToHost);
+  // waited for on failure too: the upload reads `lists`
+  const hipError_t es = hipStreamSynchronize(c->stream);
+  HIP_TRY(c, e == hipSuccess ? es : e, "cross_sections");
   return MQCT_OK;
 }
 

@@ -6,6 +6,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 namespace mqct {
 
 namespace {
@@ -155,6 +157,7 @@ level_sum_kernel(int N, const double* __restrict__ P, const int32_t* __restrict_
 // partial sums meet in wave order.  Bound by the latency of the scan: B = 4096, 81
 // levels: 13 us (one thread per (L', L'') over all trajectories took 291 us).
 constexpr int XS_CHUNK = 1024;
+constexpr int64_t XS_GRID = 1 << 20;
 __global__ void __launch_bounds__(256)
 xsec_kernel(int64_t B, const double* __restrict__ bpar, const int32_t* __restrict__ init_level,
             int n_levels, double b_max, const double* __restrict__ level_sums,
@@ -340,15 +343,18 @@ hipError_t launch_xsec(int64_t B, int N, const double* P, const double* b,
                        const int32_t* init_level, const int32_t* off, const int32_t* chan,
                        int n_levels, double b_max, double* level_sums, double* sigma,
                        hipStream_t s) {
-  if (B > 0x7fffffffLL || (n_levels + 63) / 64 > 65535) return hipErrorInvalidValue;
-  // a row of at most 32 KiB leaves several workgroups per compute unit
-  if (N <= 4096)
-    level_sum_kernel<true><<<(unsigned)B, 256, (size_t)N * 8, s>>>(N, P, off, chan, n_levels,
-                                                                   level_sums);
-  else
-    level_sum_kernel<false><<<(unsigned)B, 256, 0, s>>>(N, P, off, chan, n_levels, level_sums);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if ((n_levels + 63) / 64 > 65535) return hipErrorInvalidValue;
+  // a row of at most 32 KiB leaves several workgroups per compute unit; grid.x holds one
+  // trajectory a workgroup, XS_GRID a launch
+  for (int64_t b0 = 0; b0 < B; b0 += XS_GRID) {
+    const unsigned n = (unsigned)std::min<int64_t>(B - b0, XS_GRID);
+    const double* p = P + b0 * N;
+    double* ls = level_sums + b0 * n_levels;
+    if (N <= 4096) level_sum_kernel<true><<<n, 256, (size_t)N * 8, s>>>(N, p, off, chan, n_levels, ls);
+    else level_sum_kernel<false><<<n, 256, 0, s>>>(N, p, off, chan, n_levels, ls);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   xsec_kernel<<<dim3((unsigned)n_levels, (unsigned)((n_levels + 63) / 64)), 256, 0, s>>>(
       B, b, init_level, n_levels, b_max, level_sums, sigma);
   return hipGetLastError();
