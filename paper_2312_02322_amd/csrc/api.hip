@@ -2005,7 +2005,10 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
                   what, r, JMAX);
   if (!finite_arr(d->b, (int64_t)n1 * bs) || !finite_arr(d->v, (int64_t)T * K))
     return fail(c, MQCT_ERR_NONFINITE, "%s: non-finite b or v", what);
-  std::vector<int32_t> level((size_t)(JMAX + 1) * (JMAX + 1) * (MMAX + 1), -1);
+  int j1m = 0, j2m = 0;
+  for (int r = 0; r < n1; ++r) j1m = std::max(j1m, (int)d->rot1_j[r]);
+  for (int n = 0; n < N; ++n) j2m = std::max(j2m, std::min((int)d->j2[n], JMAX));
+  std::vector<int32_t> level((size_t)(j1m + 1) * (j2m + 1) * (j1m + j2m + 1), -1);
   std::vector<int32_t> jl_j1, jl_j2, jl_j, chan_J(N);
   int64_t of_m[2 * MMAX + 1] = {};   // channels of each m
   int cg_lmax = 0, cg_jmax = 0;
@@ -2016,7 +2019,7 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
     if (j2 < 0 || j2 > JMAX || j < std::abs(j1 - j2) || j > j1 + j2 || std::abs(m) > j)
       return fail(c, MQCT_ERR_ARG, "%s: channel %d: need 0 <= j2 <= %d, |j1-j2| <= j <= j1+j2, "
                   "|m| <= j", what, n, JMAX);
-    int32_t& lv = level[((size_t)j1 * (JMAX + 1) + j2) * (MMAX + 1) + j];
+    int32_t& lv = level[((size_t)j1 * (j2m + 1) + j2) * (j1m + j2m + 1) + j];
     if (lv < 0) {
       lv = (int32_t)jl_j1.size();
       jl_j1.push_back(j1);

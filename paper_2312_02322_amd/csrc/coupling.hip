@@ -255,6 +255,10 @@ __device__ __forceinline__ bool work_item(const CouplingDev& d, int2& w) {
 // each); this form 0.69 ms.  What is left is neither its products (0.56 without) nor its
 // stores (0.60 without) but the latency of the gathers at three waves per SIMD; two tiles
 // a wave (230 registers) take 0.74 ms, a persistent grid 0.68.
+// Beyond FILL_TC terms v is staged again for each 16 channels of a wave, beyond FILL_KC
+// knots the factors are read again, and both stay ahead of the per-lane form (whole builds,
+// N = 2,475: 97 terms 1.51 -> 1.20 ms, 240 terms 2.43 -> 1.56, 83 terms and 200 knots 3.80
+// -> 2.66, 192 and 200 6.14 -> 3.86).
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
 constexpr int FILL_TC = 96, FILL_KC = 64, FILL_LD = FILL_KC + 4;
@@ -293,10 +297,11 @@ cpl_fill(CouplingDev d, double* __restrict__ M, double* __restrict__ G) {
         const int nt = min(FILL_TC, T - c0);
         if (h == 0 || T > FILL_TC) {
           __syncthreads();
-          for (int i = threadIdx.x; i < FILL_TC * FILL_KC; i += FILL_BLOCK) {
-            const int t = i / FILL_KC, k = i % FILL_KC;
-            vl[t * FILL_LD + k] = t < nt && k0 + k < K ? d.v[(int64_t)(c0 + t) * KP + k0 + k] : 0.0;
-          }
+          if (M)
+            for (int i = threadIdx.x; i < FILL_TC * FILL_KC; i += FILL_BLOCK) {
+              const int t = i / FILL_KC, k = i % FILL_KC;
+              vl[t * FILL_LD + k] = t < nt && k0 + k < K ? d.v[(int64_t)(c0 + t) * KP + k0 + k] : 0.0;
+            }
           if (threadIdx.x < FILL_TC) tl[threadIdx.x] = d.t_l[min(c0 + (int)threadIdx.x, T - 1)];
           __syncthreads();
         }
