@@ -102,7 +102,13 @@ enum {
 };
 
 /* Create a context on HIP device `device`.  `hip_stream` is a hipStream_t to
- * enqueue all work on (NULL: the context creates and owns its own stream). */
+ * enqueue all work on (NULL: the context creates and owns its own stream).
+ * A context keeps the device workspace of its calls for the next ones until it is
+ * destroyed: as much as a run on BINNED or COLUMNS or a gradient has asked for, up to
+ * 1 GiB for fixed steps that MQCT_SCHED_AUTO sends to BINNED and for
+ * mqct_system_set_theta (one shared workspace; set_theta gives back what it takes
+ * beyond 1 GiB).  Where an allocation of the context finds no memory, that workspace is
+ * given back first. */
 mqct_status mqct_create(int32_t device, void* hip_stream, mqct_context** out);
 /* Free every device buffer of the context (waits for its stream first). */
 void mqct_destroy(mqct_context* ctx);

@@ -66,7 +66,7 @@ static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 // for the error paths, from the environment (read at every call):
 // MQCT_FAULT=alloc fails each allocation as out of device memory;
 // MQCT_FAULT=alloc@n fails only the n-th allocation counted from the call that
-// first saw that value.
+// first saw that value.  (Injected failures are final: nothing is given back for them.)
 template <typename T>
 hipError_t dev_malloc(T** p, size_t bytes) {
   static std::string seen;
@@ -150,6 +150,24 @@ mqct_status hip_fail(mqct_context* c, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(ctx, e_, what); \
   } while (0)
 
+// A device allocation for this context.  The workspace that calls share (binws) holds
+// nothing between calls and stays with the context for the next one; where memory runs out
+// it is given back first.  No call allocates anything else once it uses that workspace.
+// MQCT_FAULT=full (see dev_malloc) refuses every allocation while there is something to give
+// back.
+template <typename T>
+hipError_t ctx_malloc(mqct_context* c, T** p, size_t bytes) {
+  const char* f = getenv("MQCT_FAULT");
+  const bool full = f && strcmp(f, "full") == 0 && c->binws.p;
+  hipError_t e = full ? hipErrorOutOfMemory : dev_malloc(p, bytes);
+  if (e != hipErrorOutOfMemory || !c->binws.p || (f && !full)) return e;
+  (void)hipGetLastError();
+  if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
+  hipFree(c->binws.p);
+  c->binws = DevBuf{};
+  return dev_malloc(p, bytes);
+}
+
 mqct_status ensure(mqct_context* c, DevBuf& b, size_t bytes, const char* what) {
   if (bytes <= b.cap) return MQCT_OK;
   if (b.p) {
@@ -160,7 +178,7 @@ mqct_status ensure(mqct_context* c, DevBuf& b, size_t bytes, const char* what) {
     b.cap = 0;
   }
   size_t want = std::max(bytes, (size_t)4096);
-  HIP_TRY(c, dev_malloc(&b.p, want), what);
+  HIP_TRY(c, ctx_malloc(c, &b.p, want), what);
   b.cap = want;
   return MQCT_OK;
 }
@@ -207,7 +225,7 @@ mqct_status upload_systems(mqct_context* c) {
     if (c->d_systems) hipFree(c->d_systems);
     c->d_systems = nullptr;
     size_t want = bytes * 2;
-    HIP_TRY(c, dev_malloc((void**)&c->d_systems, want), "system table");
+    HIP_TRY(c, ctx_malloc(c, (void**)&c->d_systems, want), "system table");
     c->d_systems_cap = want;
   }
   HIP_TRY(c, hipMemcpyAsync(c->d_systems, h.data(), h.size() * sizeof(DevSystem),
@@ -452,14 +470,14 @@ mqct_status mqct_system_load(mqct_context* c, const mqct_system_desc* d, int32_t
   };
   hipError_t e;
   if (d->M_mem == MQCT_MEM_HOST) {
-    if ((e = dev_malloc((void**)&din, in_elems * 8)) != hipSuccess) return dfail(e, "system_load: input");
+    if ((e = ctx_malloc(c, (void**)&din, in_elems * 8)) != hipSuccess) return dfail(e, "system_load: input");
     own_in = true;
     if ((e = hipMemcpy(din, d->M, in_elems * 8, hipMemcpyHostToDevice)) != hipSuccess)
       return dfail(e, "system_load: upload");
   } else {
     din = (double*)d->M;
   }
-  if ((e = dev_malloc((void**)&stats, 3 * sizeof(unsigned long long))) != hipSuccess)
+  if ((e = ctx_malloc(c, (void**)&stats, 3 * sizeof(unsigned long long))) != hipSuccess)
     return dfail(e, "system_load: stats");
   if ((e = hipMemsetAsync(stats, 0, 3 * sizeof(unsigned long long), c->stream)) != hipSuccess)
     return dfail(e, "system_load: stats");
@@ -482,14 +500,14 @@ mqct_status mqct_system_load(mqct_context* c, const mqct_system_desc* d, int32_t
                 herm, 1e-12 * amax);
   }
   // storage, spline curvature, small arrays
-  if ((e = dev_malloc(&sh.bufs[0], store_elems * es)) != hipSuccess) return dfail(e, "system_load: tables");
-  if ((e = dev_malloc(&sh.bufs[1], store_elems * es)) != hipSuccess) return dfail(e, "system_load: tables");
-  if ((e = dev_malloc(&sh.bufs[2], K * 8)) != hipSuccess) return dfail(e, "system_load: grid");
-  if ((e = dev_malloc(&sh.bufs[3], N * 8)) != hipSuccess) return dfail(e, "system_load: energies");
+  if ((e = ctx_malloc(c, &sh.bufs[0], store_elems * es)) != hipSuccess) return dfail(e, "system_load: tables");
+  if ((e = ctx_malloc(c, &sh.bufs[1], store_elems * es)) != hipSuccess) return dfail(e, "system_load: tables");
+  if ((e = ctx_malloc(c, &sh.bufs[2], K * 8)) != hipSuccess) return dfail(e, "system_load: grid");
+  if ((e = ctx_malloc(c, &sh.bufs[3], N * 8)) != hipSuccess) return dfail(e, "system_load: energies");
   int64_t per_col = (int64_t)N * Npad * ncomp;
   int64_t tmp_doubles = std::min<int64_t>((int64_t)K * per_col, (int64_t)64 << 20);
   tmp_doubles = std::max<int64_t>(tmp_doubles, K);
-  if ((e = dev_malloc((void**)&tmp, tmp_doubles * 8)) != hipSuccess) return dfail(e, "system_load: scratch");
+  if ((e = ctx_malloc(c, (void**)&tmp, tmp_doubles * 8)) != hipSuccess) return dfail(e, "system_load: scratch");
   if ((e = hipMemcpy(sh.bufs[2], d->R_grid, K * 8, hipMemcpyHostToDevice)) != hipSuccess)
     return dfail(e, "system_load: grid");
   if ((e = hipMemcpy(sh.bufs[3], d->E, N * 8, hipMemcpyHostToDevice)) != hipSuccess)
@@ -505,8 +523,8 @@ mqct_status mqct_system_load(mqct_context* c, const mqct_system_desc* d, int32_t
       if (amax) hipFree(amax);
       return dfail(err, what);
     };
-    if ((e = dev_malloc((void**)&amax, (size_t)N * N * 8)) != hipSuccess) return efail(e, "system_load: pattern");
-    if ((e = dev_malloc(&sh.ebuf[1], (size_t)N * 4)) != hipSuccess) return efail(e, "system_load: pattern");
+    if ((e = ctx_malloc(c, (void**)&amax, (size_t)N * N * 8)) != hipSuccess) return efail(e, "system_load: pattern");
+    if ((e = ctx_malloc(c, &sh.ebuf[1], (size_t)N * 4)) != hipSuccess) return efail(e, "system_load: pattern");
     if ((e = launch_ell_pattern(din, N, K, ncomp, d->drop_below, amax, (int*)sh.ebuf[1], c->stream)) != hipSuccess)
       return efail(e, "system_load: pattern");
     std::vector<int> cnt(N);
@@ -518,11 +536,11 @@ mqct_status mqct_system_load(mqct_context* c, const mqct_system_desc* d, int32_t
     void* E = nullptr;
     void* E2 = nullptr;
     const size_t ebytes = (size_t)K * Wm * Npad * ncomp * es;
-    if ((e = dev_malloc(&sh.ebuf[0], (size_t)Wm * Npad * 4)) != hipSuccess) return efail(e, "system_load: slots");
+    if ((e = ctx_malloc(c, &sh.ebuf[0], (size_t)Wm * Npad * 4)) != hipSuccess) return efail(e, "system_load: slots");
     if ((e = launch_ell_fill(amax, N, Npad, Wm, d->drop_below, (int32_t*)sh.ebuf[0], c->stream)) != hipSuccess)
       return efail(e, "system_load: slots");
-    if ((e = dev_malloc(&E, ebytes)) != hipSuccess) return efail(e, "system_load: sparse tables");
-    if ((e = dev_malloc(&E2, ebytes)) != hipSuccess) { hipFree(E); return efail(e, "system_load: sparse tables"); }
+    if ((e = ctx_malloc(c, &E, ebytes)) != hipSuccess) return efail(e, "system_load: sparse tables");
+    if ((e = ctx_malloc(c, &E2, ebytes)) != hipSuccess) { hipFree(E); return efail(e, "system_load: sparse tables"); }
     if ((e = launch_ell_gather(sh.bufs[0], sh.bufs[1], (const int32_t*)sh.ebuf[0], (const int*)sh.ebuf[1],
                                N, Npad, K, Wm, ncomp, d->storage, E, E2, c->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(c->stream)) != hipSuccess) {
@@ -541,8 +559,8 @@ mqct_status mqct_system_load(mqct_context* c, const mqct_system_desc* d, int32_t
     sh.table_bytes = 2 * (int64_t)ebytes;
   }
   if (W > 0) {
-    if ((e = dev_malloc(&sh.bufs[4], jx_col_h.size() * 4)) != hipSuccess) return dfail(e, "system_load: J_x");
-    if ((e = dev_malloc(&sh.bufs[5], jx_val_h.size() * 8)) != hipSuccess) return dfail(e, "system_load: J_x");
+    if ((e = ctx_malloc(c, &sh.bufs[4], jx_col_h.size() * 4)) != hipSuccess) return dfail(e, "system_load: J_x");
+    if ((e = ctx_malloc(c, &sh.bufs[5], jx_val_h.size() * 8)) != hipSuccess) return dfail(e, "system_load: J_x");
     if ((e = hipMemcpy(sh.bufs[4], jx_col_h.data(), jx_col_h.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(sh.bufs[5], jx_val_h.data(), jx_val_h.size() * 8, hipMemcpyHostToDevice)) != hipSuccess)
       return dfail(e, "system_load: J_x");
@@ -678,22 +696,22 @@ mqct_status mqct_system_load_coo(mqct_context* c, const mqct_coo_desc* d, int32_
   hipError_t e;
   if (d->mem == MQCT_MEM_HOST) {
     const size_t in_bytes = (size_t)K * d->ld * NC * 8;
-    if ((e = dev_malloc((void**)&din, in_bytes)) != hipSuccess) return dfail(e, "system_load_coo: input");
+    if ((e = ctx_malloc(c, (void**)&din, in_bytes)) != hipSuccess) return dfail(e, "system_load_coo: input");
     own_in = true;
     if ((e = hipMemcpy(din, d->values, in_bytes, hipMemcpyHostToDevice)) != hipSuccess)
       return dfail(e, "system_load_coo: upload");
   } else {
     din = (double*)d->values;
   }
-  if ((e = dev_malloc((void**)&d_perm, nnz * 4)) != hipSuccess ||
-      (e = dev_malloc((void**)&d_partner, nnz * 4)) != hipSuccess ||
-      (e = dev_malloc((void**)&stats, 3 * sizeof(unsigned long long))) != hipSuccess ||
-      (e = dev_malloc((void**)&v64, (size_t)K * nreal * 8)) != hipSuccess ||
-      (e = dev_malloc((void**)&c64, (size_t)K * nreal * 8)) != hipSuccess ||
-      (e = dev_malloc(&sh.bufs[2], K * 8)) != hipSuccess ||
-      (e = dev_malloc(&sh.bufs[3], N * 8)) != hipSuccess ||
-      (e = dev_malloc(&sh.ebuf[0], (size_t)(N + 1) * 4)) != hipSuccess ||
-      (e = dev_malloc(&sh.ebuf[1], (size_t)nnz * 4)) != hipSuccess)
+  if ((e = ctx_malloc(c, (void**)&d_perm, nnz * 4)) != hipSuccess ||
+      (e = ctx_malloc(c, (void**)&d_partner, nnz * 4)) != hipSuccess ||
+      (e = ctx_malloc(c, (void**)&stats, 3 * sizeof(unsigned long long))) != hipSuccess ||
+      (e = ctx_malloc(c, (void**)&v64, (size_t)K * nreal * 8)) != hipSuccess ||
+      (e = ctx_malloc(c, (void**)&c64, (size_t)K * nreal * 8)) != hipSuccess ||
+      (e = ctx_malloc(c, &sh.bufs[2], K * 8)) != hipSuccess ||
+      (e = ctx_malloc(c, &sh.bufs[3], N * 8)) != hipSuccess ||
+      (e = ctx_malloc(c, &sh.ebuf[0], (size_t)(N + 1) * 4)) != hipSuccess ||
+      (e = ctx_malloc(c, &sh.ebuf[1], (size_t)nnz * 4)) != hipSuccess)
     return dfail(e, "system_load_coo: buffers");
   if ((e = hipMemcpy(d_perm, perm.data(), nnz * 4, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(d_partner, partner.data(), nnz * 4, hipMemcpyHostToDevice)) != hipSuccess ||
@@ -731,16 +749,16 @@ mqct_status mqct_system_load_coo(mqct_context* c, const mqct_coo_desc* d, int32_
     sh.bufs[0] = v64;
     sh.bufs[1] = c64;
   } else {
-    if ((e = dev_malloc(&sh.bufs[0], (size_t)K * nreal * 4)) != hipSuccess ||
-        (e = dev_malloc(&sh.bufs[1], (size_t)K * nreal * 4)) != hipSuccess ||
+    if ((e = ctx_malloc(c, &sh.bufs[0], (size_t)K * nreal * 4)) != hipSuccess ||
+        (e = ctx_malloc(c, &sh.bufs[1], (size_t)K * nreal * 4)) != hipSuccess ||
         (e = launch_csr_cast_f32(v64, (int64_t)K * nreal, (float*)sh.bufs[0], c->stream)) != hipSuccess ||
         (e = launch_csr_cast_f32(c64, (int64_t)K * nreal, (float*)sh.bufs[1], c->stream)) != hipSuccess)
       return dfail(e, "system_load_coo: storage");
   }
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return dfail(e, "system_load_coo: spline");
   if (W > 0) {
-    if ((e = dev_malloc(&sh.bufs[4], jx_col_h.size() * 4)) != hipSuccess ||
-        (e = dev_malloc(&sh.bufs[5], jx_val_h.size() * 8)) != hipSuccess ||
+    if ((e = ctx_malloc(c, &sh.bufs[4], jx_col_h.size() * 4)) != hipSuccess ||
+        (e = ctx_malloc(c, &sh.bufs[5], jx_val_h.size() * 8)) != hipSuccess ||
         (e = hipMemcpy(sh.bufs[4], jx_col_h.data(), jx_col_h.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(sh.bufs[5], jx_val_h.data(), jx_val_h.size() * 8, hipMemcpyHostToDevice)) != hipSuccess)
       return dfail(e, "system_load_coo: J_x");
@@ -777,7 +795,7 @@ mqct_status mqct_system_set_driver(mqct_context* c, int32_t id, const double* U)
   if (!finite_arr(U, K)) return fail(c, MQCT_ERR_NONFINITE, "set_driver: non-finite U");
   HIP_TRY(c, hipSetDevice(c->device), "set_driver");
   HIP_TRY(c, hipStreamSynchronize(c->stream), "set_driver");
-  if (!sh.dbuf) HIP_TRY(c, dev_malloc(&sh.dbuf, (size_t)4 * K * sizeof(double)), "set_driver");
+  if (!sh.dbuf) HIP_TRY(c, ctx_malloc(c, &sh.dbuf, (size_t)4 * K * sizeof(double)), "set_driver");
   double* d = (double*)sh.dbuf;   // U [K], U'' [K], then 2K of elimination scratch
   HIP_TRY(c, hipMemcpyAsync(d, U, (size_t)K * sizeof(double), hipMemcpyHostToDevice, c->stream),
           "set_driver");
@@ -1645,14 +1663,14 @@ mqct_status mqct_system_set_params(mqct_context* c, int32_t id, int32_t P, const
     free_params(sh);
     return hip_fail(c, err, "set_params");
   };
-  if ((e = dev_malloc(&sh.pbufs[0], Gp.size() * 8)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc(&sh.pbufs[1], (size_t)P * K * 8)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc(&sh.pbufs[2], (size_t)P * K * 8)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc(&sh.pbufs[3], (size_t)P * 4)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc(&sh.pbufs[4], (size_t)(nG + 1) * 4)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc(&sh.pbufs[5], nnz * 4)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc(&sh.pbufs[6], nnz * 8)) != hipSuccess) return bail(e);
-  if ((e = dev_malloc((void**)&tmp, (size_t)2 * P * K * 8)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[0], Gp.size() * 8)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[1], (size_t)P * K * 8)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[2], (size_t)P * K * 8)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[3], (size_t)P * 4)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[4], (size_t)(nG + 1) * 4)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[5], nnz * 4)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, &sh.pbufs[6], nnz * 8)) != hipSuccess) return bail(e);
+  if ((e = ctx_malloc(c, (void**)&tmp, (size_t)2 * P * K * 8)) != hipSuccess) return bail(e);
   if ((e = hipMemcpy(sh.pbufs[4], goff.data(), (size_t)(nG + 1) * 4, hipMemcpyHostToDevice)) != hipSuccess ||
       (!gent.empty() &&
        ((e = hipMemcpy(sh.pbufs[5], gent.data(), gent.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
@@ -1707,7 +1725,7 @@ mqct_status mqct_system_set_theta(mqct_context* c, int32_t id, const double* the
     if (st != MQCT_OK) return st;
     w = (char*)c->binws.p;
   } else {
-    if ((e = dev_malloc(&own, off)) != hipSuccess) return hip_fail(c, e, "set_theta");
+    if ((e = ctx_malloc(c, &own, off)) != hipSuccess) return hip_fail(c, e, "set_theta");
     w = own;
   }
   double *Min = (double*)(w + o_M), *th = (double*)(w + o_th), *tmp = (double*)(w + o_tmp);
@@ -2078,7 +2096,7 @@ mqct_status coupling_setup(mqct_context* c, const mqct_coupling_desc* d, const c
   std::vector<int32_t> order(N), fillp(ng);
   HIP_TRY(c, hipSetDevice(c->device), what);
   char* w = nullptr;
-  hipError_t e = dev_malloc((void**)&w, total);
+  hipError_t e = ctx_malloc(c, (void**)&w, total);
   if (e != hipSuccess) return hip_fail(c, e, what);
   auto drop = [&](hipError_t err) {
     if (early) (void)hipStreamSynchronize(c->stream);
@@ -2210,7 +2228,7 @@ mqct_status mqct_coupling_build_sparse(mqct_context* c, const mqct_coupling_desc
   for (int t = 0; t < dev.T; ++t)
     for (int q = 0; q < n_screen; ++q) vs[(size_t)t * n_screen + q] = v_screen[(size_t)perm[t] * n_screen + q];
   char* sbuf = nullptr;
-  hipError_t e = dev_malloc((void**)&sbuf, 256 + vs.size() * 8);
+  hipError_t e = ctx_malloc(c, (void**)&sbuf, 256 + vs.size() * 8);
   if (e == hipSuccess) {
     unsigned long long* cnt = (unsigned long long*)sbuf;
     double* dvs = (double*)(sbuf + 256);
