@@ -316,11 +316,13 @@ template <> struct alignas(16) ColEnt<double, true> { double v, w; int m; int pa
 // amplitudes (and of the products: FP32 products over one 64-element chunk,
 // then FP64 sums).
 //
-// Bound by the L2's line rate and latency: the gathers read a kept element's
+// Bound by the round trips of the gathers, which read a kept element's
 // coupled row, 8 or 16 B x columns, which stays in a die's 4 MB L2 only if the rows
 // of one m-block do.  With all 100 columns side by side the largest blocks (5,300
-// rows x 800 B) did not, and the misses bound the kernel; a tile's do (19 M misses
-// of 129 M requests instead of 38 M), for the price of reading the tables once per
+// rows x 800 B) did not, and the misses bound the kernel; a tile's do (206,350 states,
+// FP32, L2 misses of requests a stage: 22 M of 104 M, with the columns side by side 38 M
+// of 136 M; the vector units are busy a third of the time, and the gathered bytes are a
+// fraction of what L1 and L2 can deliver), for the price of reading the tables once per
 // tile.  Rows are dealt to the dies in contiguous ranges of one tile.  Lanes beyond
 // a tile's columns would idle, so 64 / LPT elements run side by side.  What the
 // row's update reads, and the next chunk's elements, are requested before the

@@ -154,7 +154,8 @@ level_sum_kernel(int N, const double* __restrict__ P, const int32_t* __restrict_
 // One workgroup per L' and 64 of the L'': the trajectories started in L' are listed
 // XS_CHUNK at a time (in batch order, from wave ballots), and wave w adds entries w,
 // w + 4, ... of the list, its lanes reading 64 consecutive level sums; the four
-// partial sums meet in wave order.  Bound by the latency of the scan: B = 4096, 81
+// partial sums meet in wave order (against exact sums, 4096 trajectories on 81 levels:
+// 7e-17 relative on average, 3e-16 at most; one after the other 1.5e-16 and 6e-16).  Bound by the latency of the scan: B = 4096, 81
 // levels: 13 us (one thread per (L', L'') over all trajectories took 291 us).
 constexpr int XS_CHUNK = 1024;
 constexpr int64_t XS_GRID = 1 << 20;
