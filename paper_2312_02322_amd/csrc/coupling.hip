@@ -489,8 +489,9 @@ hipError_t launch_coupling(const CouplingDev& d, double* M, double* G, Prof* pro
                            hipStream_t s) {
   const size_t lds = (FILL_TC * FILL_LD + (size_t)(d.cg_jmax + 1) * (d.cg_lmax + 1)) * 8;
   hipError_t e = hipSuccess;
-  if (lds > 65536) e = hipFuncSetAttribute((const void*)cpl_fill,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (lds + FILL_TC * 4 > 65536)      // (the terms' lam beside it)
+    e = hipFuncSetAttribute((const void*)cpl_fill, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds);
   if (e != hipSuccess || (e = launch_factors(d, s)) != hipSuccess) return e;
   const int64_t blocks = (d.n_work + NXCD - 1) / NXCD * NXCD;
   if (prof) prof->join();      // one timed launch with the clearing of the outputs
